@@ -9,7 +9,8 @@
 //    compiled per shape.
 //  * gemm_simple: any dtype, any strides, plain FMA tiles (fp32 graphs, odd layouts).
 //  * conv_stem_kernel: convolutions with fewer than 8 input channels and 64 output channels.
-//  * gemv_f32_kernel: fp32 contractions with at most 8 rows (the gate networks).
+//  * gemm_f32_split: fp32 contractions on small grids, k split over the waves of a workgroup;
+//    gemv_f32_kernel: fp32 contractions of one row (the gate networks).
 //  * row kernels: LayerNorm and softmax with one wavefront per row, 16-byte loads, wave shuffles.
 //  * reduce_mean (plain and wide), maxpool, elementwise chains (Fig. 4).
 //  * gather, cache append, arg-max; NonZero, ScatterRows, wide row gather (batch compaction);
@@ -279,6 +280,109 @@ __global__ __launch_bounds__(256) void gemm_simple(GemmArgs g) {
       v = apply_act(v, g.act2);
       C[(long long)row * g.c_sm + (long long)col * g.c_sn] = from_f<T>(v);
     }
+  }
+}
+
+// ---------------------------------------------------------------------------------------------
+// fp32 contraction for grids that leave most of the chip idle under 64 x 64 tiles (sequences of up to a few hundred
+// rows, the gate networks' few): bound by memory latency, not by arithmetic, so the k range is what is split.  A
+// workgroup of 8 waves owns a (16 TM) x (16 TN) tile; wave w takes the w-th eighth of k, requests up to 8 chunks of 16 k
+// of both operands before the first is used (K <= 1024: one memory round trip), multiplies them on
+// v_mfma_f32_16x16x4_f32 (full fp32) and the 8 partial tiles are added in wave order through LDS.  The k a lane
+// holds: elements 4 q .. 4 q + 3 of a chunk for lane group q, one element per MFMA (the order of k inside a chunk is
+// the same for both operands, so it does not matter), which makes a k-contiguous operand one 16-byte load per chunk.
+// AV / BV: the operand is k-contiguous and 16-byte aligned; otherwise 4 loads through its strides.
+// The six contractions of an encoder block of 77 rows (hidden 256, FFN 1024) take 4.5 us each, launch included; under
+// 64 x 64 FMA tiles they took 29 us (a serial walk over k by 4 to 24 workgroups).
+// ---------------------------------------------------------------------------------------------
+constexpr int F32_WAVES = 8, F32_U = 8;
+template <int TM, int TN, bool AV, bool BV>
+__global__ __launch_bounds__(F32_WAVES * 64) void gemm_f32_split(GemmArgs g) {
+  constexpr int BM = TM * 16, BN = TN * 16, U = F32_U / (TM > 1 ? 2 : 1);
+  typedef float f32x4_t __attribute__((ext_vector_type(4)));
+  __shared__ float part[F32_WAVES][BM * BN];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, r16 = lane & 15, q = lane >> 4;
+  const int tiles_m = (g.M + BM - 1) / BM;
+  const int m0 = (blockIdx.x % tiles_m) * BM, n0 = (blockIdx.x / tiles_m) * BN;
+  const int b0 = blockIdx.y / g.nb1, b1 = blockIdx.y % g.nb1;
+  const float* A = (const float*)g.A + b0 * g.a_sb0 + b1 * g.a_sb1;
+  const float* B = (const float*)g.B + b0 * g.b_sb0 + b1 * g.b_sb1;
+  f32x4_t acc[TM][TN];
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) acc[i][j][r] = 0.f;
+  const int chunks = (g.K + 15) / 16, per = (chunks + F32_WAVES - 1) / F32_WAVES;
+  const int c_lo = wave * per, c_hi = min(chunks, c_lo + per);
+  for (int c0 = c_lo; c0 < c_hi; c0 += U) {
+    f32x4_t a[U][TM], b[U][TN];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int k = (c0 + u) * 16 + q * 4;
+      const bool on = c0 + u < c_hi;
+#pragma unroll
+      for (int i = 0; i < TM; ++i) {
+        const int m = m0 + i * 16 + r16;
+        if (AV) {
+          const f32x4_t z = {0.f, 0.f, 0.f, 0.f};
+          a[u][i] = (on && m < g.M && k < g.K) ? *(const f32x4_t*)(A + (long long)m * g.a_sm + k) : z;
+        } else {
+#pragma unroll
+          for (int e = 0; e < 4; ++e) a[u][i][e] = (on && m < g.M && k + e < g.K) ? A[(long long)m * g.a_sm + (long long)(k + e) * g.a_sk] : 0.f;
+        }
+      }
+#pragma unroll
+      for (int j = 0; j < TN; ++j) {
+        const int n = n0 + j * 16 + r16;
+        if (BV) {
+          const f32x4_t z = {0.f, 0.f, 0.f, 0.f};
+          b[u][j] = (on && n < g.N && k < g.K) ? *(const f32x4_t*)(B + (long long)n * g.b_sn + k) : z;
+        } else {
+#pragma unroll
+          for (int e = 0; e < 4; ++e) b[u][j][e] = (on && n < g.N && k + e < g.K) ? B[(long long)(k + e) * g.b_sk + (long long)n * g.b_sn] : 0.f;
+        }
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+          for (int j = 0; j < TN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[u][i][e], b[u][j][e], acc[i][j], 0, 0, 0);
+  }
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) part[wave][(i * 16 + q * 4 + r) * BN + j * 16 + r16] = acc[i][j][r];
+  // what the epilogue adds is requested ahead of the barrier
+  constexpr int PT = (BM * BN + F32_WAVES * 64 - 1) / (F32_WAVES * 64);
+  float* C = (float*)g.C + b0 * g.c_sb0 + b1 * g.c_sb1;
+  const float* R = g.res ? (const float*)g.res + b0 * g.r_sb0 + b1 * g.r_sb1 : nullptr;
+  float bias[PT], res[PT];
+#pragma unroll
+  for (int i = 0; i < PT; ++i) {
+    const int e = tid + i * F32_WAVES * 64, row = m0 + e / BN, col = n0 + e % BN;
+    const bool in = e < BM * BN && row < g.M && col < g.N;
+    bias[i] = in && g.bias ? ((const float*)g.bias)[col] : 0.f;
+    res[i] = in && R ? R[(long long)row * g.r_sm + (long long)col * g.r_sn] : 0.f;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < PT; ++i) {
+    const int e = tid + i * F32_WAVES * 64, row = m0 + e / BN, col = n0 + e % BN;
+    if (e >= BM * BN || row >= g.M || col >= g.N) continue;
+    float v = 0.f;
+#pragma unroll
+    for (int w = 0; w < F32_WAVES; ++w) v += part[w][e];
+    v = apply_act(v * g.scale + bias[i], g.act1);
+    if (R) v = apply_act(v + res[i], g.act2);
+    C[(long long)row * g.c_sm + (long long)col * g.c_sn] = v;
   }
 }
 
@@ -1335,9 +1439,8 @@ hipError_t launch_conv_dl(const ConvArgs& c, const GemmArgs& g, int tile, hipStr
 hipError_t launch_gemv(const GemmArgs& g, hipStream_t s);
 hipError_t launch_gemm_ln(const GemmArgs& g, hipStream_t s);
 
-// fp32 contraction with at most 8 rows (the gate networks of the control-flow graphs): one wave per
+// fp32 contraction of a single row (the gate networks of the control-flow graphs): one wave per
 // output column, the lanes split k in 16-byte chunks of B[n, :], a shuffle tree finishes the sums
-template <int MR>
 __global__ __launch_bounds__(256) void gemv_f32_kernel(GemmArgs g) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int n = blockIdx.x * 4 + wave;
@@ -1345,51 +1448,60 @@ __global__ __launch_bounds__(256) void gemv_f32_kernel(GemmArgs g) {
   if (n >= g.N) return;
   const float* A = (const float*)g.A + b0 * g.a_sb0 + b1 * g.a_sb1;
   const float* B = (const float*)g.B + b0 * g.b_sb0 + b1 * g.b_sb1 + (long long)n * g.b_sn;
-  float acc[MR];
-#pragma unroll
-  for (int m = 0; m < MR; ++m) acc[m] = 0.f;
+  const float bv = g.bias ? ((const float*)g.bias)[n] : 0.f;
+  float acc = 0.f;
   const int nchunk = g.K >> 2;
-  for (int c = lane; c < nchunk; c += 64) {
-    const float4 w = *(const float4*)(B + c * 4);
+  const float4 z = make_float4(0.f, 0.f, 0.f, 0.f);
+  for (int c0 = lane; c0 < nchunk; c0 += 64 * 4) {       // 4 chunks of both operands in flight
+    float4 w[4], a[4];
 #pragma unroll
-    for (int m = 0; m < MR; ++m) {
-      if (m < g.M) {
-        const float4 a = *(const float4*)(A + (long long)m * g.a_sm + c * 4);
-        acc[m] = fmaf(a.x, w.x, fmaf(a.y, w.y, fmaf(a.z, w.z, fmaf(a.w, w.w, acc[m]))));
-      }
+    for (int u = 0; u < 4; ++u) {
+      const int c = c0 + 64 * u;
+      w[u] = c < nchunk ? *(const float4*)(B + c * 4) : z;
+      a[u] = c < nchunk ? *(const float4*)(A + c * 4) : z;
     }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) acc = fmaf(a[u].x, w[u].x, fmaf(a[u].y, w[u].y, fmaf(a[u].z, w[u].z, fmaf(a[u].w, w[u].w, acc))));
   }
-#pragma unroll
-  for (int m = 0; m < MR; ++m) acc[m] = wave_sum(acc[m]);
+  acc = wave_sum(acc);
   if (lane == 0) {
-    const float bv = g.bias ? ((const float*)g.bias)[n] : 0.f;
-    float* Cp = (float*)g.C + b0 * g.c_sb0 + b1 * g.c_sb1;
-    const float* Rp = g.res ? (const float*)g.res + b0 * g.r_sb0 + b1 * g.r_sb1 : nullptr;
-#pragma unroll
-    for (int m = 0; m < MR; ++m) {
-      if (m < g.M) {
-        float v = apply_act(acc[m] * g.scale + bv, g.act1);
-        if (Rp) v = apply_act(v + Rp[(long long)m * g.r_sm + (long long)n * g.r_sn], g.act2);
-        Cp[(long long)m * g.c_sm + (long long)n * g.c_sn] = v;
-      }
-    }
+    float v = apply_act(acc * g.scale + bv, g.act1);
+    if (g.res) v = apply_act(v + ((const float*)g.res + b0 * g.r_sb0 + b1 * g.r_sb1)[(long long)n * g.r_sn], g.act2);
+    ((float*)g.C + b0 * g.c_sb0 + b1 * g.c_sb1)[(long long)n * g.c_sn] = v;
   }
 }
 
 static bool gemv_f32_ok(const Launch& L, const GemmArgs& g) {
   auto al = [](const void* p) { return ((uintptr_t)p & 15) == 0; };
-  return L.in_dtype != SOD2_BF16_TAG && L.out_dtype != SOD2_BF16_TAG && L.variant == V_GEMV && g.M <= 8 &&
+  return L.in_dtype != SOD2_BF16_TAG && L.out_dtype != SOD2_BF16_TAG && L.variant == V_GEMV && g.M <= 1 &&
          g.a_sk == 1 && g.b_sk == 1 && g.K % 4 == 0 && g.a_sm % 4 == 0 && g.b_sn % 4 == 0 && g.a_sb0 % 4 == 0 &&
          g.a_sb1 % 4 == 0 && g.b_sb0 % 4 == 0 && g.b_sb1 % 4 == 0 && al(g.A) && al(g.B);
+}
+
+template <int T>
+static hipError_t launch_f32_tile(const GemmArgs& g, bool av, bool bv, hipStream_t s) {
+  dim3 grid(((g.M + 16 * T - 1) / (16 * T)) * ((g.N + 16 * T - 1) / (16 * T)), g.nb0 * g.nb1), block(F32_WAVES * 64);
+  if (av && bv) hipLaunchKernelGGL((gemm_f32_split<T, T, true, true>), grid, block, 0, s, g);
+  else if (av) hipLaunchKernelGGL((gemm_f32_split<T, T, true, false>), grid, block, 0, s, g);
+  else if (bv) hipLaunchKernelGGL((gemm_f32_split<T, T, false, true>), grid, block, 0, s, g);
+  else hipLaunchKernelGGL((gemm_f32_split<T, T, false, false>), grid, block, 0, s, g);
+  return hipGetLastError();
+}
+// fewer than 512 tiles of 64 x 64 (two per CU): the split-k kernel, with 16 x 16 tiles as long as those fit the chip
+// four workgroups to a CU, else 32 x 32 (half the operand traffic per result); from there on 64 x 64 FMA tiles fill
+// the chip and read each operand less often
+static hipError_t launch_gemm_f32_split(const GemmArgs& g, hipStream_t s) {
+  auto al = [](const void* p) { return ((uintptr_t)p & 15) == 0; };
+  const bool av = g.a_sk == 1 && g.K % 4 == 0 && g.a_sm % 4 == 0 && g.a_sb0 % 4 == 0 && g.a_sb1 % 4 == 0 && al(g.A);
+  const bool bv = g.b_sk == 1 && g.K % 4 == 0 && g.b_sn % 4 == 0 && g.b_sb0 % 4 == 0 && g.b_sb1 % 4 == 0 && al(g.B);
+  const long long t16 = (long long)((g.M + 15) / 16) * ((g.N + 15) / 16) * g.nb0 * g.nb1;
+  return t16 <= 1024 ? launch_f32_tile<1>(g, av, bv, s) : launch_f32_tile<2>(g, av, bv, s);
 }
 
 hipError_t launch_gemm(const Launch& L, const GemmArgs& g, hipStream_t s) {
   if (g.ln_gamma) return L.in_dtype == SOD2_BF16_TAG ? launch_gemm_ln(g, s) : hipErrorInvalidValue;
   if (gemv_f32_ok(L, g)) {
-    dim3 grid((g.N + 3) / 4, g.nb0 * g.nb1);
-    if (g.M <= 1) hipLaunchKernelGGL(gemv_f32_kernel<1>, grid, dim3(256), 0, s, g);
-    else if (g.M <= 4) hipLaunchKernelGGL(gemv_f32_kernel<4>, grid, dim3(256), 0, s, g);
-    else hipLaunchKernelGGL(gemv_f32_kernel<8>, grid, dim3(256), 0, s, g);
+    hipLaunchKernelGGL(gemv_f32_kernel, dim3((g.N + 3) / 4, g.nb0 * g.nb1), dim3(256), 0, s, g);
     return hipGetLastError();
   }
   if (L.variant == V_GEMV && L.in_dtype == SOD2_BF16_TAG && g.a_vec && g.b_mode == 0 && g.M <= 8) return launch_gemv(g, s);
@@ -1398,6 +1510,7 @@ hipError_t launch_gemm(const Launch& L, const GemmArgs& g, hipStream_t s) {
   if (L.variant == V_SIMPLE || L.in_dtype != SOD2_BF16_TAG) {
     dim3 grid(((g.M + 63) / 64) * ((g.N + 63) / 64), g.nb0 * g.nb1);
     if (L.in_dtype == SOD2_BF16_TAG) hipLaunchKernelGGL(gemm_simple<bf16_t>, grid, dim3(256), 0, s, g);
+    else if (grid.x * grid.y < 512) return launch_gemm_f32_split(g, s);
     else hipLaunchKernelGGL(gemm_simple<float>, grid, dim3(256), 0, s, g);
     return hipGetLastError();
   }
