@@ -8,6 +8,7 @@
 #include <functional>
 #include <memory>
 
+#include "chain.hpp"
 #include "handles.hpp"
 
 namespace sod2 {
@@ -1606,6 +1607,21 @@ std::vector<Launch> build_launches(const Plan& p, const BindResult& b, int force
   return out;
 }
 
+// a plan whose executed groups may form one chain of one-row work (chain.hip): decided by the kinds of groups, before
+// any launch is prepared
+bool may_chain(const Plan& p, const BindResult& b) {
+  if (p.n_switches || !p.exec_ops.empty() || b.steps.size() < 8) return false;
+  for (int at : b.steps) {
+    const Item& it = p.items[at];
+    if (!it.is_group) return false;
+    switch (p.groups.at(it.ref).kind) {
+      case G_GEMM: case G_GATHER: case G_ATTENTION: case G_ARGMAX: break;
+      default: return false;
+    }
+  }
+  return true;
+}
+
 }  // namespace
 }  // namespace sod2
 
@@ -1719,6 +1735,12 @@ struct sod2_replay_s {
   hipGraphExec_t exec = nullptr;
   int* step = nullptr;
   int max_steps = 0;
+  // the step as one kernel (chain.hip) instead of a graph: the caller's buffers, their advance per step, the keys per step
+  bool chained = false;
+  Chain chain;
+  std::vector<char*> ext;
+  std::vector<int64_t> ext_step;
+  int d_lk = 0;
   ~sod2_replay_s() {
     if (exec) (void)hipGraphExecDestroy(exec);
     if (graph) (void)hipGraphDestroy(graph);
@@ -1802,6 +1824,23 @@ extern "C" sod2_status sod2_replay_create(const sod2_plan_t* ph, const int64_t* 
     r->step = step_counter;
     r->max_steps = max_steps;
     hipStream_t s = (hipStream_t)stream;
+    bool same_growth = may_chain(p, b0);
+    for (const Launch& L : L0)
+      if (L.kernel == K_ATTENTION) {
+        if (r->d_lk == 0) r->d_lk = L.d_lk;
+        same_growth = same_growth && L.d_lk == r->d_lk;
+      }
+    if (same_growth && chain_build(L0, n_inputs, n_outputs, [&](const Ref& ref) { return P.at(ref); }, chain_workgroups(),
+                                   r->d_lk * (max_steps - 1), &r->chain)) {
+      for (int i = 0; i < n_inputs; ++i) { r->ext.push_back((char*)inputs[i]); r->ext_step.push_back(P.in_step[i]); }
+      for (int i = 0; i < n_outputs; ++i) { r->ext.push_back((char*)outputs[i]); r->ext_step.push_back(P.out_step[i]); }
+      r->chained = chain_fits(r->chain, (void* const*)r->ext.data());
+      for (const ChainStep& c : r->chain.steps) if (c.out_ext >= 0 && r->ext_step[c.out_ext] % 4) r->chained = false;
+    }
+    if (r->chained) {
+      *out = r.release();
+      return SOD2_OK;
+    }
     if (hipStreamBeginCapture(s, hipStreamCaptureModeRelaxed) != hipSuccess) throw Error(SOD2_ERR_HIP, "stream capture could not start");
     hipError_t e = hipSuccess;
     for (const Launch& L : L0) {
@@ -1830,6 +1869,20 @@ extern "C" sod2_status sod2_replay_launch(sod2_replay_t* r, int32_t first_step, 
     return SOD2_ERR_INVALID_ARG;
   }
   hipStream_t s = (hipStream_t)stream;
+  if (r->chained) {
+    try {
+      std::vector<void*> ext(r->ext.size());
+      for (int i = first_step; i < first_step + n_steps; ++i) {
+        for (size_t k = 0; k < ext.size(); ++k) ext[k] = r->ext[k] + r->ext_step[k] * i;
+        chain_launch(r->chain, ext.data(), r->chain.lk0 + r->d_lk * i, s);
+      }
+      if (launch_step_set(r->step, first_step + n_steps, s) != hipSuccess) throw Error(SOD2_ERR_HIP, "step counter could not be set");
+    } catch (const sod2::Error& e) {
+      sod2::set_error(e.what());
+      return e.code;
+    }
+    return SOD2_OK;
+  }
   if (launch_step_set(r->step, first_step, s) != hipSuccess) { sod2::set_error("step counter could not be set"); return SOD2_ERR_HIP; }
   for (int i = 0; i < n_steps; ++i)
     if (hipGraphLaunch(r->exec, s) != hipSuccess) { sod2::set_error("graph launch failed"); return SOD2_ERR_HIP; }
@@ -1955,6 +2008,41 @@ static sod2_status run_impl(sod2_binding_t* h, void* arena, size_t arena_bytes, 
       }
     }
 
+    auto trace_launch = [&](const Launch& L, int ref) {
+      int splits = 1;
+      if (L.kernel == K_GEMM && P.ws) splits = std::max(L.u.gemm.splits, 1);
+      else if (L.kernel == K_CONV && P.ws) splits = std::max(L.u.conv.splits, 1);
+      int fold = 0;
+      if (L.kernel == K_GEMM && !L.empty) {
+        if (L.post_ln) fold = (L.fold_pair && P.constants) ? 1 : 3;
+        if (L.fold_read && P.constants) fold = 2;
+      }
+      h->trace.push_back(sod2_trace_entry{1, ref, L.empty ? -1 : L.kernel, L.variant, splits, -1, fold});
+    };
+
+    // One-row work from end to end (a decode step) runs as one kernel.  Not under capture: a replayed launch would carry
+    // the tags of the captured one.
+    if (!static_ws && !ev && h->force_variant < 0 && p.opts.mvc && may_chain(p, h->b)) {
+      hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+      if (hipStreamIsCapturing(s, &capture) != hipSuccess) { (void)hipGetLastError(); capture = hipStreamCaptureStatusActive; }
+      if (capture == hipStreamCaptureStatusNone) {
+        for (size_t j = 0; j < h->b.steps.size(); ++j)
+          if (h->launches[j].kernel == -2) h->launches[j] = first->make(p.groups.at(p.items[h->b.steps[j]].ref));
+        h->launches_valid = true;
+        Chain chain;
+        if (chain_build(h->launches, n_inputs, n_outputs, [&](const Ref& ref) { return P.at(ref); }, chain_workgroups(), 0, &chain)) {
+          std::vector<void*> ext;
+          for (int i = 0; i < n_inputs; ++i) ext.push_back((void*)inputs[i]);
+          for (int i = 0; i < n_outputs; ++i) ext.push_back(outputs[i]);
+          if (chain_fits(chain, ext.data())) {
+            chain_launch(chain, ext.data(), chain.lk0, s);
+            for (size_t j = 0; j < h->b.steps.size(); ++j) trace_launch(h->launches[j], p.items[h->b.steps[j]].ref);
+            return SOD2_OK;
+          }
+        }
+      }
+    }
+
     const BindResult* cur = &h->b;
     const std::vector<Launch>* launches = &h->launches;
     BindResult replanned;
@@ -2011,17 +2099,7 @@ static sod2_status run_impl(sod2_binding_t* h, void* arena, size_t arena_bytes, 
         if (e != hipSuccess) throw Error(SOD2_ERR_HIP, std::string("kernel launch failed: ") + hipGetErrorString(e));
         if (ev) { (void)hipEventRecord(ev[n_ev + 1], s); timed.push_back({n_ev, L}); n_ev += 2; }
         if (!L.empty) ++queued;
-        {
-          int splits = 1;
-          if (L.kernel == K_GEMM && P.ws) splits = std::max(L.u.gemm.splits, 1);
-          else if (L.kernel == K_CONV && P.ws) splits = std::max(L.u.conv.splits, 1);
-          int fold = 0;
-          if (L.kernel == K_GEMM && !L.empty) {
-            if (L.post_ln) fold = (L.fold_pair && P.constants) ? 1 : 3;
-            if (L.fold_read && P.constants) fold = 2;
-          }
-          h->trace.push_back(sod2_trace_entry{1, it.ref, L.empty ? -1 : L.kernel, L.variant, splits, -1, fold});
-        }
+        trace_launch(L, it.ref);
         if (L.kernel == K_NONZERO || L.kernel == K_NMS) {
           // the extent is execution determined: read the count back, then size and plan what follows
           const bool is_nms = L.kernel == K_NMS;

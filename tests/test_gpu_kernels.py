@@ -51,3 +51,56 @@ def test_fp32_contraction(S, M, N, K, trans_b, batch):
     # K products and the two additions, each rounded once, in any order: (K + 3) half-ulps of the sum of magnitudes
     bound = (K + 3) * 2.0 ** -24 * (np.abs(X) @ np.abs(Wt) + np.abs(B) + np.abs(Rs))
     assert got.shape == ref.shape and (np.abs(got - ref) <= bound).all(), np.max(np.abs(got - ref) / bound)
+
+
+# The decode step as one kernel against the same launches one by one: widths that deal out to 256, 192 and 128
+# workgroups, cache lengths at the edges of the parts of 128 keys an attention workgroup takes, one and many parts.
+@pytest.mark.parametrize("hidden,heads,ffn,vocab,P", [(512, 8, 1024, 1000, 126), (768, 12, 3072, 2002, 1), (1024, 16, 4096, 32000, 383),
+                                                      (512, 8, 2560, 998, 511), (768, 12, 1536, 5000, 250)])
+def test_decode_step_as_one_kernel(S, hidden, heads, ffn, vocab, P):
+    import torch
+    from paper_2403_00176_amd.session import DecoderSession
+    from workloads import configs
+    print(f"case hidden {hidden} heads {heads} ffn {ffn} vocab {vocab} P {P}", flush=True)
+    steps = 6
+    w = configs.decoder(layers=2, hidden=hidden, heads=heads, ffn=ffn, vocab=vocab, p_range=(1, 512), t_max=steps + 2, n_prompts=1)
+    ses = DecoderSession(w.prefill, w.decode, w.t_max)
+    ses.upload_weights(w.make_weights_by_name())
+    ses.start(P, vocab)
+    ses.prefill(torch.from_numpy(np.random.RandomState(P).randint(0, vocab, P)).to(ses.device))
+    forced = torch.from_numpy(np.random.RandomState(P + 1).randint(0, vocab, steps)).to(ses.device)
+    torch.cuda.synchronize()
+
+    def run(one_by_one):
+        for t in range(steps):
+            with torch.cuda.stream(ses.stream):
+                ses.tokens[P + t] = forced[t]                    # teacher forcing: both paths see the same tokens
+            b = ses.dec.bind({"P": P, "t": t})
+            if one_by_one:
+                S.sod2_binding_force_variant(b, 6)
+            ses.decode(t, b)
+        torch.cuda.synchronize()
+        d = w.decode
+        caches = [ses.arena[at:at + (P + steps) * hidden * 2].view(torch.bfloat16).float().clone()
+                  for at in (S.sod2_binding_query_tensor(b, t)["offset"] for t in d.session_inputs())]
+        return ses.logits[1:steps + 1].float().clone(), ses.tokens[P + 1:P + steps + 1].clone(), caches
+
+    ref, one = run(True), run(False)
+    # both round every operator's row to bf16, sums in another order: a value next to a rounding boundary may fall on
+    # either side (2^-8), and passes through at most 10 more roundings of its own size: far below the 2e-2 of the oracle
+    for a, b in [(ref[0], one[0])] + list(zip(ref[2], one[2])):
+        assert torch.isfinite(b).all()
+        assert ((a - b).norm() / a.norm()).item() <= 2 ** -8, ((a - b).norm() / a.norm()).item()
+    # the token behind the last step is the arg-max of that step's logits, the lowest index among equals
+    last = one[0][steps - 1]
+    assert int(one[1][steps - 1]) == int((last == last.max()).nonzero()[0])
+    # the same steps as a replay, bit for bit
+    ses.logits.zero_()
+    with torch.cuda.stream(ses.stream):
+        ses.tokens[P] = forced[0]
+    ses.decode(0)
+    torch.cuda.synchronize()
+    row = ses.logits[1].clone()
+    ses.decode_replay(0, 1)
+    torch.cuda.synchronize()
+    assert torch.equal(row, ses.logits[1])
