@@ -4,16 +4,22 @@
 // v_mfma_f32_32x32x16_bf16.  The A operand comes from a loader (a strided matrix, or an NHWC
 // im2col address generator: the convolution is an implicit GEMM on the same main loop).
 //
-// Data movement: every lane issues global_load_lds_dwordx4, which copies 16 bytes from a per-lane
-// global address straight into LDS at (M0 base + lane * 16): no staging registers, no LDS store
-// instructions.  A ring of ST stages keeps ST-1 k-tiles in flight per workgroup, one barrier per
-// k-tile.  Because the hardware fixes the LDS position of a lane, the XOR swizzle that keeps the
-// MFMA fragment reads free of bank conflicts is applied on the global side: the lane that owns LDS
-// slot s of row r fetches k-chunk s ^ f(r).  Rows past M, k past K and padding taps of a convolution
-// fetch from a 16-byte block of zeros, so tails need no masking in the main loop.
+// Data movement: every lane issues buffer_load_dwordx4 ... lds, which copies 16 bytes from a per-lane
+// offset into a buffer straight into LDS at (M0 base + lane * 16): no staging registers, no LDS store
+// instructions.  A lane's offset stays the same from k-tile to k-tile, only the scalar offset moves, so a
+// k-tile costs no address arithmetic (a convolution's changes when the tap does).  A ring of ST stages keeps
+// ST-1 k-tiles in flight per workgroup, one barrier per k-tile.  Because the hardware fixes the LDS position
+// of a lane, the XOR swizzle that keeps the MFMA fragment reads free of bank conflicts is applied on the
+// global side: the lane that owns LDS slot s of row r fetches k-chunk s ^ f(r).  Rows past M, k past K and
+// padding taps of a convolution use an offset outside the buffer, for which the hardware writes zeros, so
+// tails need no masking in the main loop.
 //
 // Loads are written as inline assembly together with their wait counts: the compiler would
 // otherwise wait for *all* outstanding loads before any LDS read, which serialises the ring.
+//
+// What the epilogue adds or multiplies by (bias, residual, LayerNorm parameters and statistics) is requested before
+// the ring is filled and first touched behind the k loop: a wait for such a load in front of the loop is also a wait
+// for whatever the ring has requested before it, 1 - 3 us per launch where the operands are cold.
 //
 // Split-K (gridDim.z > 1): each z computes a k range and stores its fp32 partial tile to a
 // workspace; splitk_reduce, launched behind it, sums the partials in the order z = 0, 1, ... and
@@ -27,56 +33,78 @@
 
 namespace sod2 {
 
-static __device__ __attribute__((aligned(256))) uint4 g_zero_chunk[16];   // never written: all zero
-
 template <int KV> __device__ __forceinline__ int swz(int row, int c) {
   if (KV == 8) return c ^ ((row >> 1) & 7);                           // 128-byte rows (measured conflict free; row & 7 is not)
   return c ^ ((row >> 1) & 3) ^ ((row >> 3) & 1);                     // 64-byte rows: two rows share a bank line
 }
 
-// ---- A-operand loaders: address of the 8 elements at k = (current tile) + kc of one row, or null ----
+// A buffer that starts at a 64-bit address all lanes agree on.  Valid offsets are below 2^31 (the launcher checks the
+// operands); OUTSIDE is not, and reads as zero.
+typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
+constexpr uint32_t OUTSIDE = 0x80000000u;
+__device__ __forceinline__ u32x4_t buffer_at(const void* p) {
+  const uint64_t a = (uint64_t)p;
+  u32x4_t r;
+  r[0] = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)a);
+  r[1] = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(a >> 32));      // stride 0
+  r[2] = 0x7fffffffu;
+  r[3] = 0x00020000u;                                                             // 32-bit data
+  return r;
+}
+__device__ __forceinline__ void load_lds16(u32x4_t buf, uint32_t voff, uint32_t soff, uint32_t lds_wave_base) {
+  // LDS address of lane l = lds_wave_base + 16 * l
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" ::"s"(lds_wave_base), "v"(voff), "s"(buf), "s"(soff)
+               : "memory");
+}
+// n / d for n < 2^31 by a multiplication (m, s from the launcher's quick_div)
+__device__ __forceinline__ int quot(int n, QuickDiv d) { return (int)(__umulhi((uint32_t)n << 1, d.m) >> d.s); }
+
+// ---- A-operand loaders: per row the lane's offset in the buffer at the current k-tile ----
 struct DlMat {
   const bf16_t* p;
   long long sm;
-  int M, K, k0;
-  struct Row { const bf16_t* ptr; };
-  __device__ __forceinline__ void init_row(Row& r, int m) const { r.ptr = m < M ? p + (long long)m * sm : nullptr; }
-  __device__ __forceinline__ void tile(int k) { k0 = k; }
-  __device__ __forceinline__ const bf16_t* addr(const Row& r, int kc) const {
-    return (r.ptr && k0 + kc < K) ? r.ptr + k0 + kc : nullptr;
-  }
+  int M;
+  struct Row { uint32_t off; };
+  __device__ __forceinline__ u32x4_t open(int m0) { return buffer_at(p + (long long)m0 * sm); }
+  __device__ __forceinline__ void init_row(Row& r, int m0, int row, int kc) const { r.off = m0 + row < M ? (uint32_t)(row * (int)sm + kc) * 2u : OUTSIDE; }
+  __device__ __forceinline__ void start(int k) {}
+  __device__ __forceinline__ void advance(int dk) {}
+  __device__ __forceinline__ uint32_t scalar_off(int k) const { return (uint32_t)k * 2u; }
+  __device__ __forceinline__ uint32_t off(const Row& r) const { return r.off; }
 };
 struct DlConv {                     // x[nb, ih, iw, c], k = (kh * KW + kw) * C + c; needs C % BK == 0
   const bf16_t* p;
   int H, W, C, KW, stride, pad, OH, OW, M, K;
+  QuickDiv d_ow, d_oh, d_c, d_kw;
   int kh, kw, c0;
-  struct Row { const bf16_t* img; int ih0, iw0; };
-  __device__ __forceinline__ void init_row(Row& r, int m) const {
-    if (m >= M) { r.img = nullptr; r.ih0 = r.iw0 = 0; return; }
-    int ow = m % OW, t = m / OW;
-    int oh = t % OH, nb = t / OH;
-    r.img = p + (long long)nb * H * W * C;
-    r.ih0 = oh * stride - pad;
+  struct Row { int base, ih0, iw0; };
+  __device__ __forceinline__ u32x4_t open(int) { return buffer_at(p); }
+  __device__ __forceinline__ void init_row(Row& r, int m0, int row, int kc) const {
+    const int m = m0 + row, t = quot(m, d_ow), ow = m - t * OW, nb = quot(t, d_oh), oh = t - nb * OH;
+    r.ih0 = m < M ? oh * stride - pad : -0x40000000;
     r.iw0 = ow * stride - pad;
+    r.base = (((nb * H + oh * stride - pad) * W + r.iw0) * C + kc) * 2;
   }
-  __device__ __forceinline__ void tile(int k) {
-    if (k >= K) { kh = -0x40000000; kw = 0; c0 = 0; return; }       // past the end: every tap is outside
-    int kk = k / C;
+  __device__ __forceinline__ void start(int k) {
+    const int kk = quot(k, d_c);
     c0 = k - kk * C;
-    kh = kk / KW;
+    kh = quot(kk, d_kw);
     kw = kk - kh * KW;
   }
-  __device__ __forceinline__ const bf16_t* addr(const Row& r, int kc) const {
-    int ih = r.ih0 + kh, iw = r.iw0 + kw;
-    if (!r.img || ih < 0 || ih >= H || iw < 0 || iw >= W) return nullptr;
-    return r.img + ((long long)ih * W + iw) * C + c0 + kc;
+  __device__ __forceinline__ void advance(int dk) {
+    c0 += dk;
+    while (c0 >= C) {
+      c0 -= C;
+      if (++kw == KW) { kw = 0; ++kh; }
+    }
+  }
+  __device__ __forceinline__ uint32_t scalar_off(int) const { return (uint32_t)c0 * 2u; }
+  __device__ __forceinline__ uint32_t off(const Row& r) const {
+    const bool in = (uint32_t)(r.ih0 + kh) < (uint32_t)H && (uint32_t)(r.iw0 + kw) < (uint32_t)W;
+    return in ? (uint32_t)(r.base + (kh * W + kw) * C * 2) : OUTSIDE;
   }
 };
 
-__device__ __forceinline__ void load_lds16(const void* gptr, uint32_t lds_wave_base) {
-  // LDS address of lane l = lds_wave_base + 16 * l
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(lds_wave_base), "v"(gptr) : "memory");
-}
 template <int N> __device__ __forceinline__ void wait_loads() {
   asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
 }
@@ -100,6 +128,10 @@ __device__ __forceinline__ float quad_sum(float v) {
   v += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0xB1, 0xF, 0xF, false));   // lanes 1 0 3 2
   v += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x4E, 0xF, 0xF, false));   // lanes 2 3 0 1
   return v;
+}
+
+__device__ __forceinline__ float pair_sum(float v) {            // lanes 2 q and 2 q + 1
+  return v + __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0xB1, 0xF, 0xF, false));
 }
 
 // The second result of a contraction with a LayerNorm behind it, for the 8 consecutive columns a lane has just stored
@@ -200,9 +232,12 @@ __global__ __launch_bounds__(LW * KG * 64, OCC * LW * KG / 4) void gemm_dl(AL al
   static_assert((ST - 2) * LT <= 63, "vmcnt is a 6-bit counter");
   // behind the ring: FOLD 1 the tile's BN values of gamma; FOLD 2 per tile row (scale * rstd, -scale * rstd * mean),
   // then the tile's BN values of fold_s and of fold_c (staged here so that no register holds them through the k loop)
-  __shared__ __attribute__((aligned(16))) bf16_t lds[LDS_ELEMS + (FOLD == 2 ? BM * 4 + BN * 4 : (FOLD == 1 ? BN : 0))];
-  float* rowstat = (float*)(lds + LDS_ELEMS);
-  float* colc = rowstat + BM * 2;
+  // behind the ring: FOLD 1 the tile's BN values of gamma; FOLD 2 the tile's BN values of fold_s and of fold_c, then per
+  // tile row (scale * rstd, -scale * rstd * mean).  (In LDS, so that no register holds them through the k loop.)
+  constexpr int AUX = FOLD == 2 ? 1024 * ((BN + 127) / 128) : (FOLD == 1 ? 1024 : 0);     // bytes: whole 1 KB loads
+  __shared__ __attribute__((aligned(16))) bf16_t lds[LDS_ELEMS + AUX / 2 + (FOLD == 2 ? BM * 4 : 0)];
+  float* colc = (float*)(lds + LDS_ELEMS);
+  float* rowstat = (float*)(lds + LDS_ELEMS + AUX / 2);
   bf16_t* gam_lds = lds + LDS_ELEMS;
 
   const int tid = threadIdx.x, lane = tid & 63;
@@ -221,23 +256,91 @@ __global__ __launch_bounds__(LW * KG * 64, OCC * LW * KG / 4) void gemm_dl(AL al
   }
   int tm, tn;
   {
-    const int gm = g.group_m, per = gm * tiles_n;
-    const int panel = lid / per, rem = lid - panel * per;
-    const int pm0 = panel * gm, w = min(gm, tiles_m - pm0);
-    tm = pm0 + rem % w;
-    tn = rem / w;
+    const int gm = g.group_m, panel = quot(lid, g.d_panel), rem = lid - panel * gm * tiles_n, pm0 = panel * gm;
+    tn = quot(rem, pm0 + gm <= tiles_m ? g.d_group : g.d_last);             // (the last panel may have fewer rows)
+    tm = pm0 + rem - tn * min(gm, tiles_m - pm0);
   }
-  const int b0 = blockIdx.y / g.nb1, b1 = blockIdx.y % g.nb1;
+  int b0 = 0, b1 = 0;
+  if (gridDim.y > 1) { b0 = blockIdx.y / g.nb1; b1 = blockIdx.y % g.nb1; }
   const int m0 = tm * BM, n0 = tn * BN;
 
   al.p += b0 * g.a_sb0 + b1 * g.a_sb1;
   const bf16_t* Bp = (const bf16_t*)g.B + b0 * g.b_sb0 + b1 * g.b_sb1;
+  bf16_t* Cp = (bf16_t*)g.C + b0 * g.c_sb0 + b1 * g.c_sb1;
+  const bf16_t* Rp = g.res ? (const bf16_t*)g.res + b0 * g.r_sb0 + b1 * g.r_sb1 : nullptr;
+  const bool partials = gridDim.z > 1;
 
   // k range of this split
   const int nk_all = (g.K + BK * KG - 1) / (BK * KG);         // steps: one k-tile per group and step
-  const int per_split = (nk_all + gridDim.z - 1) / gridDim.z;
+  const int per_split = partials ? (int)((nk_all + gridDim.z - 1) / gridDim.z) : nk_all;
   const int kt0 = blockIdx.z * per_split;
   const int nk = max(0, min(per_split, nk_all - kt0));
+
+  const uint32_t lds_base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)lds;
+
+  // ---- requests whose results are used behind the k loop ----
+  // the epilogue's 8 columns of this lane, their bias and (where there are registers) the residual of its rows; the
+  // 256-row tile that runs four waves per SIMD, 128 registers each, has none to spare
+  constexpr bool PRE = !(BM * BN >= 256 * 128 && OCC * LW * KG / 4 > 2);
+  constexpr int CG = EW / 8, QN = 32 * CG / 64;
+  static_assert(64 % CG == 0 && QN >= 1, "a lane keeps one column group through the epilogue");
+  const int ecg = lane % CG, er0 = lane / CG;
+  const int ecol = n0 + wn * EW + ecg * 8;
+  const bool ecol_full = g.c_vec && ecol + 8 <= g.N;
+  const bool rfull = Rp && !partials && ecol_full;              // residual rows as 16-byte vectors
+  V16 ebv, egam;
+  u32x4_t rv[2][QN];
+  auto res_fetch = [&](int i, int buf) {
+    const int roww = m0 + wm * TM * 32 + i * 32;
+#pragma unroll
+    for (int q = 0; q < QN; ++q) {
+      const int row = roww + er0 + q * (64 / CG);
+      const u32x4_t z = {0u, 0u, 0u, 0u};
+      rv[buf][q] = (rfull && row < g.M) ? *(const u32x4_t*)(Rp + (long long)row * g.r_sm + ecol) : z;
+    }
+  };
+  constexpr bool EARLY_RES = PRE && QN <= 4;                    // the first 32 rows' residual: 16 registers at most
+  if (PRE && (KG == 1 || kg == 0)) {
+    ebv.u = (g.bias && ecol_full) ? *(const uint4*)((const bf16_t*)g.bias + ecol) : zero4();
+    if (EARLY_RES && rfull) res_fetch(0, 0);
+  }
+  // FOLD 2: TPR threads per tile row add up the row's partial statistics (one pair per run of 32 columns of the operand,
+  // stored behind its M x K elements as [run][row]): mean = S / K, variance = (sum of the runs' squared distances
+  // from their own means + sum of s_j^2 / 32 - S^2 / K) / K.  Up to SL pairs per thread wait in registers; a longer row
+  // (K > 32 SL TPR) adds up its first pairs here.
+  constexpr int TPR = NT * KG / BM, SL = 8;
+  float2 sv[FOLD == 2 ? SL : 1];
+  float s1 = 0.f, s2 = 0.f, m2 = 0.f;
+  if (FOLD == 2) {
+    static_assert(FOLD != 2 || TPR == 2 || TPR == 4 || TPR == 8, "lanes of a row are neighbours within a half row of lanes");
+    const int P = g.K >> 5, row = m0 + tid / TPR, part = tid % TPR;
+    const float2* pr = (const float2*)((const bf16_t*)g.A + (long long)g.M * g.K) + row;
+    int j0 = part;
+    for (; j0 + (SL - 1) * TPR < P - TPR; j0 += SL * TPR) {
+      float2 v[SL];
+#pragma unroll
+      for (int u = 0; u < SL; ++u) v[u] = row < g.M ? pr[(long long)(j0 + TPR * u) * g.M] : make_float2(0.f, 0.f);
+#pragma unroll
+      for (int u = 0; u < SL; ++u) { s1 += v[u].x; s2 = fmaf(v[u].x, v[u].x, s2); m2 += v[u].y; }
+    }
+#pragma unroll
+    for (int u = 0; u < SL; ++u)
+      sv[u] = (row < g.M && j0 + TPR * u < P) ? pr[(long long)(j0 + TPR * u) * g.M] : make_float2(0.f, 0.f);
+  }
+  if (FOLD && wave_all == 0) {                                  // gamma, or s and c, straight to LDS
+#pragma unroll
+    for (int q = 0; q < AUX / 1024; ++q) {
+      if (FOLD == 1) {
+        const int col = n0 + lane * 8;
+        load_lds16(buffer_at(g.fold_gamma), (lane * 8 < BN && col + 8 <= g.N) ? (uint32_t)col * 2u : OUTSIDE, 0, lds_base + LDS_ELEMS * 2);
+      } else {
+        const int e = q * 256 + lane * 4, col = n0 + e % BN;    // BN values of s, then BN of c
+        const uint32_t at = col + 4 <= g.N ? (uint32_t)col * 4u : OUTSIDE;
+        // (fold_c lies N floats behind fold_s)
+        load_lds16(buffer_at(g.fold_s), e < BN ? at : (e < 2 * BN && at != OUTSIDE ? at + (uint32_t)g.N * 4u : OUTSIDE), 0, lds_base + LDS_ELEMS * 2 + q * 1024);
+      }
+    }
+  }
 
   // fixed per thread: load j moves the 16 bytes of LDS position p of a stage (A rows first, then B rows):
   // row p / KV, slot p % KV, k-chunk (slot ^ f(row)).  When both operands divide evenly among the
@@ -245,54 +348,53 @@ __global__ __launch_bounds__(LW * KG * 64, OCC * LW * KG / 4) void gemm_dl(AL al
   // waves than one operand has 1 KB blocks) a wave-uniform flag tells which operand a load belongs to.
   constexpr bool EVEN = (BM * KV) % NT == 0 && (BN * KV) % NT == 0;
   constexpr int LA = EVEN ? BM * KV / NT : 0;
+  const u32x4_t abuf = al.open(m0), bbuf = buffer_at(Bp + (long long)n0 * g.b_sn);
   typename AL::Row arow[EVEN ? (LA > 0 ? LA : 1) : LT];
-  const bf16_t* brow[EVEN ? (LT - LA > 0 ? LT - LA : 1) : LT];
-  int kc[LT];
+  uint32_t brow[EVEN ? (LT - LA > 0 ? LT - LA : 1) : LT];
   bool is_a[LT];
-#pragma unroll
-  for (int j = 0; j < LT; ++j) {
-    int row, slot;
+  auto place = [&](int j, int& row, int& kc) {
+    int p;
     if (EVEN) {
       is_a[j] = j < LA;
-      const int p = ((is_a[j] ? j : j - LA) * NWV + wave) * 64 + lane;
+      p = ((is_a[j] ? j : j - LA) * NWV + wave) * 64 + lane;
       row = p / KV;
-      slot = p % KV;
     } else {
-      const int p = (j * NWV + wave) * 64 + lane;
+      p = (j * NWV + wave) * 64 + lane;
       is_a[j] = __builtin_amdgcn_readfirstlane(p / KV) < BM;
       row = is_a[j] ? p / KV : p / KV - BM;
-      slot = p % KV;
     }
-    kc[j] = swz<KV>(row, slot) * 8;
-    if (is_a[j]) {
-      al.init_row(arow[EVEN ? j : j], m0 + row);
-      if (!EVEN) brow[j] = nullptr;
-    } else {
-      if (!EVEN) al.init_row(arow[j], 0x7fffffff);
-      brow[EVEN ? j - LA : j] = (n0 + row < g.N) ? Bp + (long long)(n0 + row) * g.b_sn : nullptr;
-    }
+    kc = swz<KV>(row, p % KV) * 8;
+  };
+#pragma unroll
+  for (int j = 0; j < LT; ++j) {
+    int row, kc;
+    place(j, row, kc);
+    if (is_a[j]) al.init_row(arow[j], m0, row, kc);
+    else brow[EVEN ? j - LA : j] = n0 + row < g.N ? (uint32_t)(row * (int)g.b_sn + kc) * 2u : OUTSIDE;
   }
-  const uint32_t lds_base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)lds;
-  const bf16_t* zero = (const bf16_t*)g_zero_chunk;
-
-  auto issue = [&](int t, int stage) {                         // k-tile t of this split into a stage
-    const int k0 = ((kt0 + t) * KG + kg) * BK;
-    al.tile(t < nk ? k0 : g.K);
+  al.start(min((kt0 * KG + kg) * BK, g.K));
+  int t_next = 0;                                               // tiles are requested in order
+  auto issue = [&](int stage) {                                 // the next k-tile of this split into a stage
+    const int k0 = ((kt0 + t_next) * KG + kg) * BK;
+    ++t_next;
     const uint32_t sa = lds_base + (stage * KG + kg) * (STAGE * 2) + wave * 1024;
+    const uint32_t a_s = al.scalar_off(k0), b_s = (uint32_t)k0 * 2u;
+    const bool whole = k0 + BK <= g.K;
 #pragma unroll
     for (int j = 0; j < LT; ++j) {
-      const bf16_t* src;
-      if (is_a[j]) {
-        src = al.addr(arow[j], kc[j]);
-      } else {
-        const bf16_t* br = brow[EVEN ? j - LA : j];
-        src = (br && t < nk && k0 + kc[j] < g.K) ? br + k0 + kc[j] : nullptr;
+      uint32_t v = is_a[j] ? al.off(arow[j]) : brow[EVEN ? j - LA : j];
+      if (!whole) {                                             // chunks past K (all of them where a group has no tile left)
+        int row, kc;
+        place(j, row, kc);
+        if (k0 + kc >= g.K) v = OUTSIDE;
       }
       // even split: the B region starts right after the A rows; uneven: one run of positions over both
       const uint32_t dst = EVEN ? (is_a[j] ? sa + j * (NWV * 1024) : sa + BM * BK * 2 + (j - LA) * (NWV * 1024))
                                 : sa + j * (NWV * 1024);
-      load_lds16(src ? src : zero, dst);
+      if (is_a[j]) load_lds16(abuf, v, a_s, dst);
+      else load_lds16(bbuf, v, b_s, dst);
     }
+    al.advance(BK * KG);
   };
 
   f32x16_t acc[TM][TN];
@@ -302,18 +404,6 @@ __global__ __launch_bounds__(LW * KG * 64, OCC * LW * KG / 4) void gemm_dl(AL al
     for (int j = 0; j < TN; ++j)
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-
-  // epilogue operands that do not depend on the accumulators: this lane's 8 columns and their bias, fetched here,
-  // ahead of the main loop, by the kernels that have the registers to keep them (the 256-row tile that runs four
-  // waves per SIMD, 128 registers each, has none to spare)
-  constexpr bool PRE = !(BM * BN >= 256 * 128 && OCC * LW * KG / 4 > 2);
-  constexpr int CG = EW / 8, QN = 32 * CG / 64;
-  static_assert(64 % CG == 0 && QN >= 1, "a lane keeps one column group through the epilogue");
-  const int ecg = lane % CG, er0 = lane / CG;
-  const int ecol = n0 + wn * EW + ecg * 8;
-  const bool ecol_full = g.c_vec && ecol + 8 <= g.N;
-  V16 ebv, egam;
-  if (PRE) ebv.u = (g.bias && ecol_full) ? *(const uint4*)((const bf16_t*)g.bias + ecol) : zero4();
 
   // MFMA fragments are double buffered in registers: the LDS reads of k-step ks+1 are issued before
   // the MFMAs of k-step ks, and the ring's global loads go out between the first fragment reads and
@@ -350,52 +440,19 @@ __global__ __launch_bounds__(LW * KG * 64, OCC * LW * KG / 4) void gemm_dl(AL al
         acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[buf][i].b, bf[buf][j].b, acc[i][j], 0, 0, 0);
   };
 
-  // ring: tiles t .. t+ST-2 are in flight while tile t is computed.  Loads past the last tile are
-  // still issued (they fetch zeros into a stage nobody reads again), so the wait counts stay uniform.
+  // ring: tiles t .. t+ST-2 are in flight while tile t is computed; the last tiles wait for what is left
 #pragma unroll
-  for (int s = 0; s < ST - 1; ++s) issue(s, s);
-  if (FOLD == 1 && tid < BN / 8)
-    *(uint4*)&gam_lds[tid * 8] = (n0 + tid * 8 + 8 <= g.N) ? *(const uint4*)((const bf16_t*)g.fold_gamma + n0 + tid * 8) : zero4();
-  if (FOLD == 2) {
-    if (tid < BN / 4) {
-      const bool in = n0 + tid * 4 + 4 <= g.N;
-      *(float4*)&colc[tid * 4] = in ? *(const float4*)((const float*)g.fold_s + n0 + tid * 4) : make_float4(0, 0, 0, 0);
-      *(float4*)&colc[BN + tid * 4] = in ? *(const float4*)((const float*)g.fold_c + n0 + tid * 4) : make_float4(0, 0, 0, 0);
-    }
-    // four threads per tile row add up the row's partial statistics (one pair per run of 32 columns of the operand,
-    // stored behind its M x K elements as [run][row]): mean = S / K, variance = (sum of the runs' squared distances
-    // from their own means + sum of s_j^2 / 32 - S^2 / K) / K.  (These 8 K / 32 bytes per row are three quarters of a
-    // k-tile's traffic for K = 768: what the read side of a folded LayerNorm costs.)
-    const int P = g.K >> 5;
-    const float2* st = (const float2*)((const bf16_t*)g.A + (long long)g.M * g.K);
-    for (int idx = tid; idx < BM * 4; idx += NT * KG) {
-      const int row = idx >> 2, part = idx & 3;
-      float s1 = 0.f, s2 = 0.f, m2 = 0.f;
-      if (m0 + row < g.M) {
-        const float2* pr = st + (m0 + row);
-        // 8 loads in flight at a time (a loop over a run-time count would wait for each load in turn)
-        for (int j0 = part; j0 < P; j0 += 32) {
-          float2 v[8];
-#pragma unroll
-          for (int u = 0; u < 8; ++u) v[u] = (j0 + 4 * u < P) ? pr[(long long)(j0 + 4 * u) * g.M] : make_float2(0.f, 0.f);
-#pragma unroll
-          for (int u = 0; u < 8; ++u) { s1 += v[u].x; s2 = fmaf(v[u].x, v[u].x, s2); m2 += v[u].y; }
-        }
-      }
-      s1 = quad_sum(s1); s2 = quad_sum(s2); m2 = quad_sum(m2);
-      const float inv_k = 1.f / (float)g.K, mean = s1 * inv_k;
-      const float var = fmaxf((m2 + s2 * (1.f / 32.f) - s1 * mean) * inv_k, 0.f);
-      const float a = g.scale * rsqrtf(var + g.ln_eps);
-      if (part == 0) *(float2*)&rowstat[row * 2] = make_float2(a, -a * mean);
-    }
-  }
+  for (int s = 0; s < ST - 1; ++s) if (s < nk) issue(s);
   int rd = 0, wr = ST - 1;
   for (int t = 0; t < nk; ++t) {
-    wait_loads<(ST - 2) * LT>();                         // tile t has landed (this wave's part)
+    const int behind = min(ST - 2, nk - 1 - t);          // requested tiles behind tile t
+    if (ST >= 3 && behind == ST - 2) wait_loads<(ST - 2) * LT>();
+    else if (ST >= 4 && behind == 1) wait_loads<LT>();
+    else wait_loads<0>();                                       // tile t has landed (this wave's part)
     __syncthreads();                                            // ... everyone's part; stage wr is free again
     const bf16_t* S = lds + (rd * KG + kg) * STAGE;
     if (LW == NCW || wave < NCW) frag_load(S, 0, 0);
-    issue(t + ST - 1, wr);
+    if (t + ST - 1 < nk) issue(wr);
     if (LW == NCW || wave < NCW) {
 #pragma unroll
       for (int ks = 0; ks < KS; ++ks) {
@@ -405,6 +462,17 @@ __global__ __launch_bounds__(LW * KG * 64, OCC * LW * KG / 4) void gemm_dl(AL al
     }
     rd = (rd + 1 == ST) ? 0 : rd + 1;
     wr = (wr + 1 == ST) ? 0 : wr + 1;
+  }
+  if (FOLD == 2) {                                              // the rows' statistics, for the epilogue
+#pragma unroll
+    for (int u = 0; u < SL; ++u) { s1 += sv[u].x; s2 = fmaf(sv[u].x, sv[u].x, s2); m2 += sv[u].y; }
+    if (TPR == 8) { s1 = octet_sum(s1); s2 = octet_sum(s2); m2 = octet_sum(m2); }
+    else if (TPR == 4) { s1 = quad_sum(s1); s2 = quad_sum(s2); m2 = quad_sum(m2); }
+    else { s1 = pair_sum(s1); s2 = pair_sum(s2); m2 = pair_sum(m2); }
+    const float inv_k = 1.f / (float)g.K, mean = s1 * inv_k;
+    const float var = fmaxf((m2 + s2 * (1.f / 32.f) - s1 * mean) * inv_k, 0.f);
+    const float a = g.scale * rsqrtf(var + g.ln_eps);
+    if (tid % TPR == 0) *(float2*)&rowstat[(tid / TPR) * 2] = make_float2(a, -a * mean);
   }
   wait_loads<0>();
   __syncthreads();                                              // the stages become the epilogue patches
@@ -440,9 +508,7 @@ __global__ __launch_bounds__(LW * KG * 64, OCC * LW * KG / 4) void gemm_dl(AL al
   }
   // ---- epilogue: 32 rows of the wave tile at a time through a wave-private fp32 LDS patch ----
   float* patch = (float*)lds + wave * 32 * ELD;
-  bf16_t* Cp = (bf16_t*)g.C + b0 * g.c_sb0 + b1 * g.c_sb1;
-  const bf16_t* Rp = g.res ? (const bf16_t*)g.res + b0 * g.r_sb0 + b1 * g.r_sb1 : nullptr;
-  float* Wp = gridDim.z > 1 ? (float*)g.ws + ((long long)blockIdx.z * gridDim.y + blockIdx.y) * (long long)g.M * g.N : nullptr;
+  float* Wp = partials ? (float*)g.ws + ((long long)blockIdx.z * gridDim.y + blockIdx.y) * (long long)g.M * g.N : nullptr;
   auto store_partial = [&](const float* x, int row, int col) {  // fp32 partial sums of this k range
     float* w = Wp + (long long)row * g.N + col;
     if ((g.N & 3) == 0 && col + 8 <= g.N) {
@@ -465,17 +531,7 @@ __global__ __launch_bounds__(LW * KG * 64, OCC * LW * KG / 4) void gemm_dl(AL al
     // A lane owns the same 8 columns in every pass (EW / 8 divides 64): its bias values were fetched before the
     // main loop, and the residual values of the next 32 rows are fetched while the current rows are converted
     // and stored, so the epilogue pays one memory latency instead of one per pass.
-    const bool rfull = Rp && !Wp && ecol_full;                  // residual rows as 16-byte vectors
-    uint4 rv[2][QN];
-    auto res_fetch = [&](int i, int buf) {
-      const int roww = m0 + wm * TM * 32 + i * 32;
-#pragma unroll
-      for (int q = 0; q < QN; ++q) {
-        const int row = roww + er0 + q * (64 / CG);
-        rv[buf][q] = (rfull && row < g.M) ? *(const uint4*)(Rp + (long long)row * g.r_sm + ecol) : zero4();
-      }
-    };
-    if (rfull) res_fetch(0, 0);
+    if (!EARLY_RES && rfull) res_fetch(0, 0);
 #pragma unroll
     for (int i = 0; i < TM; ++i) {
 #pragma unroll
@@ -508,7 +564,7 @@ __global__ __launch_bounds__(LW * KG * 64, OCC * LW * KG / 4) void gemm_dl(AL al
           }
           act8(x, g.act1);
           if (Rp) {
-            V16 r8; r8.u = rv[i & 1][q];
+            V16 r8; r8.u = __builtin_bit_cast(uint4, rv[i & 1][q]);
 #pragma unroll
             for (int e = 0; e < 8; ++e) x[e] += bf2f(r8.h[e]);
             act8(x, g.act2);
@@ -798,12 +854,30 @@ hipError_t launch_gemv(const GemmArgs& g, hipStream_t s) {
 // ---------------------------------------------------------------------------------------------
 // host-side launchers
 // ---------------------------------------------------------------------------------------------
+// multiplier and shift of n / d for 0 <= n < 2^31: with 2^l >= d > 2^(l - 1), m = floor(2^(31 + l) / d) + 1 exceeds the
+// exact ratio by at most 1, so n m / 2^(31 + l) exceeds n / d by less than 1 / d (a power of two needs no excess)
+static QuickDiv quick_div(int d) {
+  int l = 0;
+  while ((1ll << l) < d) ++l;
+  return {(uint32_t)(((1ull << 31) << l) / (unsigned)d + (d & (d - 1) ? 1 : 0)), (uint32_t)l};
+}
+// byte offsets within a tile (plus the row) and of a convolution's input stay below 2^31
+bool dl_offsets_fit(const GemmArgs& g) {
+  const long long lim = 0x7fffffffll;
+  return (256 * g.a_sm + g.K) * 2 < lim && (256 * g.b_sn + g.K) * 2 < lim && g.a_sm > 0 && g.b_sn > 0;
+}
+
 template <class AL, int BM, int BN, int BK, int ST, int WM, int WN, int OCC, int LW = WM * WN, int KG = 1, int FOLD = 0>
 static hipError_t launch_dl(const AL& al, const GemmArgs& g, hipStream_t s) {
   const int tiles = ((g.M + BM - 1) / BM) * ((g.N + BN - 1) / BN);
   const int splits = g.splits > 1 ? g.splits : 1;
+  const int tiles_m = (g.M + BM - 1) / BM, tiles_n = (g.N + BN - 1) / BN, last = tiles_m % g.group_m;
   dim3 grid(tiles, g.nb0 * g.nb1, splits);
-  hipLaunchKernelGGL((gemm_dl<AL, BM, BN, BK, ST, WM, WN, OCC, LW, KG, FOLD>), grid, dim3(LW * KG * 64), 0, s, al, g);
+  GemmArgs a = g;
+  a.d_panel = quick_div(g.group_m * tiles_n);
+  a.d_group = quick_div(g.group_m);
+  a.d_last = quick_div(last ? last : 1);
+  hipLaunchKernelGGL((gemm_dl<AL, BM, BN, BK, ST, WM, WN, OCC, LW, KG, FOLD>), grid, dim3(LW * KG * 64), 0, s, al, a);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || splits == 1) return e;
   const long long nvec = (long long)g.M * ((g.N + 7) / 8);
@@ -866,13 +940,14 @@ static hipError_t launch_dl_fold(const DlMat& al, const GemmArgs& g, int tile, h
   }
 }
 hipError_t launch_gemm_dl(const GemmArgs& g, int tile, hipStream_t s) {
-  DlMat al{(const bf16_t*)g.A, g.a_sm, g.M, g.K, 0};
+  DlMat al{(const bf16_t*)g.A, g.a_sm, g.M};
   if (g.fold == 1) return (g.N % 32 == 0 && g.c_vec) ? launch_dl_fold<1>(al, g, tile, s) : hipErrorInvalidValue;
   if (g.fold == 2) return (g.K % 32 == 0 && g.N % 8 == 0 && g.c_vec && g.splits <= 1) ? launch_dl_fold<2>(al, g, tile, s) : hipErrorInvalidValue;
   return launch_dl_variant(al, g, tile, s);
 }
 hipError_t launch_conv_dl(const ConvArgs& c, const GemmArgs& g, int tile, hipStream_t s) {
-  DlConv al{(const bf16_t*)c.x, c.H, c.W, c.C, c.KW, c.stride, c.pad, c.OH, c.OW, g.M, g.K, 0, 0, 0};
+  DlConv al{(const bf16_t*)c.x, c.H, c.W, c.C, c.KW, c.stride, c.pad, c.OH, c.OW, g.M, g.K,
+            quick_div(c.OW), quick_div(c.OH), quick_div(c.C), quick_div(c.KW), 0, 0, 0};
   return launch_dl_variant(al, g, tile, s);
 }
 

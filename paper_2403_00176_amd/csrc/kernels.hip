@@ -1435,6 +1435,7 @@ static hipError_t launch_mfma_variant(const AL& al, const GemmArgs& g, int varia
 
 hipError_t launch_gemm_dl(const GemmArgs& g, int tile, hipStream_t s);
 hipError_t launch_conv_dl(const ConvArgs& c, const GemmArgs& g, int tile, hipStream_t s);
+bool dl_offsets_fit(const GemmArgs& g);
 
 hipError_t launch_gemv(const GemmArgs& g, hipStream_t s);
 hipError_t launch_gemm_ln(const GemmArgs& g, hipStream_t s);
@@ -1505,7 +1506,7 @@ hipError_t launch_gemm(const Launch& L, const GemmArgs& g, hipStream_t s) {
     return hipGetLastError();
   }
   if (L.variant == V_GEMV && L.in_dtype == SOD2_BF16_TAG && g.a_vec && g.b_mode == 0 && g.M <= 8) return launch_gemv(g, s);
-  if (L.variant >= V_DL0 && L.in_dtype == SOD2_BF16_TAG && g.a_vec && g.b_mode == 0)
+  if (L.variant >= V_DL0 && L.in_dtype == SOD2_BF16_TAG && g.a_vec && g.b_mode == 0 && dl_offsets_fit(g))
     return launch_gemm_dl(g, L.variant - V_DL0, s);
   if (L.variant == V_SIMPLE || L.in_dtype != SOD2_BF16_TAG) {
     dim3 grid(((g.M + 63) / 64) * ((g.N + 63) / 64), g.nb0 * g.nb1);
@@ -1634,13 +1635,16 @@ hipError_t launch_conv(const Launch& L, const ConvArgs& c, hipStream_t s) {
   GemmArgs g{};
   g.M = c.NB * c.OH * c.OW; g.N = c.O; g.K = c.KH * c.KW * c.C;
   g.nb0 = g.nb1 = 1;
+  g.a_sm = 1;
   g.B = c.w; g.b_sk = 1; g.b_sn = g.K; g.b_mode = (g.K % 8 == 0 && ((uintptr_t)c.w & 15) == 0) ? 0 : 2;
   g.C = c.y; g.c_sm = c.O; g.c_sn = 1;
   g.bias = c.bias; g.res = c.res; g.r_sm = c.O; g.r_sn = 1;
   g.scale = 1.f; g.act1 = c.act1; g.act2 = c.act2;
   g.c_vec = (c.O % 8 == 0) && (((uintptr_t)c.y & 15) == 0) && (!c.bias || ((uintptr_t)c.bias & 15) == 0) &&
             (!c.res || ((uintptr_t)c.res & 15) == 0);
-  if (L.variant >= V_DL0 && c.vec && c.C % 64 == 0 && g.b_mode == 0) {
+  // (offsets into the input are 32-bit there)
+  if (L.variant >= V_DL0 && c.vec && c.C % 64 == 0 && g.b_mode == 0 && dl_offsets_fit(g) &&
+      (double)c.NB * (c.H + 2.0 * c.pad) * (c.W + 2.0 * c.pad) * c.C * 2.0 < 2.0e9) {
     g.group_m = 8;
     if (c.splits > 1 && c.ws) { g.splits = c.splits; g.ws = c.ws; }
     return launch_conv_dl(c, g, L.variant - V_DL0, s);

@@ -24,6 +24,8 @@ enum DlTile { DL_128x128x64_S3_W4 = 0, DL_128x128x64_S2_W4, DL_128x128x32_S3_W4,
               DL_256x256x32_S3_W8, DL_64x64x64_S4_L8, DL_64x64x64_S4_L16, DL_128x128x64_S2_L16, DL_64x128x64_S3_L8, DL_256x256x64_S2_W8, DL_256x128x64_S3_W8,
               DL_64x64x64_S4_G2, DL_64x64x64_S3_G2, DL_64x64x64_S2_G4, DL_128x128x64_S2_G2, DL_64x64x64_S2_G2, DL_128x128x64_S2_W8G2, DL_128x128x64_S2_W8T, DL_128x128x64_S3_W8T, DL_TILES };   // _Gn: n wave groups split k inside the workgroup
 
+struct QuickDiv { uint32_t m, s; };     // division of a non-negative int: the high half of a product, shifted
+
 // C[b0,b1,m,n] = act2( act1( scale * sum_k A[b0,b1,m,k] * B[b0,b1,k,n] + bias[n] ) + R[b0,b1,m,n] )
 struct GemmArgs {
   const void* A; const void* B; void* C; const void* bias; const void* res;
@@ -38,6 +40,7 @@ struct GemmArgs {
   int c_vec;               // c_sn == 1 and rows 4-byte aligned
   int splits;              // > 1: split-K, fp32 partials in ws, summed in z order by a second kernel
   int group_m;             // tile rows per panel of the tile walk (L2 locality)
+  QuickDiv d_panel, d_group, d_last;   // tiles of a panel; rows of a panel, of the last panel
   void* ws;                // split-K workspace: splits x batch x M x N floats
   const int* step;         // replay (skinny kernel only): C advances by *step * c_step elements
   long long c_step;
