@@ -1735,7 +1735,7 @@ struct sod2_replay_s {
   hipGraphExec_t exec = nullptr;
   int* step = nullptr;
   int max_steps = 0;
-  // the step as one kernel (chain.hip) instead of a graph: the caller's buffers, their advance per step, the keys per step
+  // the step as one kernel (chain.hip), taken instead of the graph outside capture: the caller's buffers, their advance per step, the keys per step
   bool chained = false;
   Chain chain;
   std::vector<char*> ext;
@@ -1837,10 +1837,7 @@ extern "C" sod2_status sod2_replay_create(const sod2_plan_t* ph, const int64_t* 
       r->chained = chain_fits(r->chain, (void* const*)r->ext.data());
       for (const ChainStep& c : r->chain.steps) if (c.out_ext >= 0 && r->ext_step[c.out_ext] % 4) r->chained = false;
     }
-    if (r->chained) {
-      *out = r.release();
-      return SOD2_OK;
-    }
+    // (the graph is there for a chained step too: sod2_replay_launch on a stream that is being captured takes it)
     if (hipStreamBeginCapture(s, hipStreamCaptureModeRelaxed) != hipSuccess) throw Error(SOD2_ERR_HIP, "stream capture could not start");
     hipError_t e = hipSuccess;
     for (const Launch& L : L0) {
@@ -1869,7 +1866,14 @@ extern "C" sod2_status sod2_replay_launch(sod2_replay_t* r, int32_t first_step, 
     return SOD2_ERR_INVALID_ARG;
   }
   hipStream_t s = (hipStream_t)stream;
-  if (r->chained) {
+  // one kernel per step, but not under capture: a captured launch run again would carry the tags of its first run
+  bool chained = r->chained;
+  if (chained) {
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &capture) != hipSuccess) { (void)hipGetLastError(); capture = hipStreamCaptureStatusActive; }
+    chained = capture == hipStreamCaptureStatusNone;
+  }
+  if (chained) {
     try {
       std::vector<void*> ext(r->ext.size());
       for (int i = first_step; i < first_step + n_steps; ++i) {
