@@ -660,7 +660,6 @@ struct ChainDevice {
   unsigned* err_dev = nullptr;
   hipEvent_t last = nullptr;                // recorded behind the newest launch
   bool any = false;
-  hipStream_t last_stream = nullptr;
   unsigned next_tag = 1;
   std::vector<ChainStep> held[CH_TABLES];   // what the device tables hold
   uint64_t used[CH_TABLES] = {}, clock = 0;
@@ -733,7 +732,8 @@ void chain_launch(const Chain& c, void* const* ext, int lk, hipStream_t s) {
   first_use(d);
   if (__atomic_load_n(d.err_host, __ATOMIC_RELAXED))
     throw Error(SOD2_ERR_HIP, "a one-row step waited too long for another workgroup: its results and what was computed from them are not valid");
-  if (d.any && d.last_stream != s) need(hipStreamWaitEvent(s, d.last, 0), "ordering one-row steps of two streams");
+  // on the same stream too: a handle may by now be another stream's (destroyed and created again, or the per-thread one)
+  if (d.any) need(hipStreamWaitEvent(s, d.last, 0), "ordering one-row steps of two streams");
   int slot = -1, oldest = 0;
   const size_t bytes = c.steps.size() * sizeof(ChainStep);
   for (int i = 0; i < CH_TABLES; ++i) {
@@ -770,7 +770,6 @@ void chain_launch(const Chain& c, void* const* ext, int lk, hipStream_t s) {
   need(hipGetLastError(), "one-row step");
   need(hipEventRecord(d.last, s), "one-row step");
   d.any = true;
-  d.last_stream = s;
 }
 
 // the rows that go to the caller's buffers are written two values at a time
@@ -843,9 +842,10 @@ bool chain_build(const std::vector<Launch>& launches, int n_in, int n_out, const
       s.beta = ln ? at(L.r[6]) : nullptr;
       s.eps = g.ln_eps; s.scale = g.scale; s.act1 = g.act1; s.act2 = g.act2;
       if (g.M != 1 || g.nb0 * g.nb1 != 1 || L.in_dtype != SOD2_BF16 || L.out_dtype != SOD2_BF16 || g.a_sk != 1 || g.b_sk != 1 || g.c_sn != 1 ||
-          g.K % 8 || g.K > CHAIN_MAX_K || (ln && g.K > 1024) || g.b_sn % 8 || g.b_sn > 0x7fffffff || g.N % 2 || L.post_ln || L.fold_read ||
+          g.K % 8 || g.K > CHAIN_MAX_K || (ln && g.K > 1024) || g.b_sn % 8 || g.b_sn > (1 << 20) || g.N % 2 || L.post_ln || L.fold_read ||
           L.r[1].space != SP_WEIGHT || !al(s.w, 16) || !al(s.bias, 4) || !al(s.gamma, 16) || !al(s.beta, 16))
         return false;
+      // (up to 1024 rows of a workgroup, 2 bytes an element: offsets stay within 32 bits)
       while ((512 << s.seg_shift) < g.K) ++s.seg_shift;
       if (st.empty()) return false;          // (a chain starts with an embedding row)
       s.src = (int)st.size() - 1;

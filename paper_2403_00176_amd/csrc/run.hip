@@ -483,7 +483,8 @@ struct Builder {
   static bool dl_can_fold(int variant) {
     switch (variant - V_DL0) {
       case DL_256x256x64_S2_W8: case DL_256x128x32_S3_W8: case DL_128x128x64_S3_W8T:
-      case DL_128x128x64_S2_W8T: case DL_64x64x64_S3_G2: case DL_64x64x64_S2_G2: case DL_64x64x64_S4_W4: return true;
+      case DL_128x128x64_S2_W8T: case DL_64x64x64_S3_G2: case DL_64x64x64_S2_G2: case DL_64x64x64_S4_W4:
+      case DL_32x32x32_S4_G8: case DL_64x32x32_S3_G8: return true;
       default: return false;
     }
   }
@@ -1884,6 +1885,9 @@ extern "C" sod2_status sod2_replay_launch(sod2_replay_t* r, int32_t first_step, 
     } catch (const sod2::Error& e) {
       sod2::set_error(e.what());
       return e.code;
+    } catch (const std::exception& e) {
+      sod2::set_error(e.what());
+      return SOD2_ERR_INVALID_ARG;
     }
     return SOD2_OK;
   }

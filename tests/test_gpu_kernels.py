@@ -104,3 +104,33 @@ def test_decode_step_as_one_kernel(S, hidden, heads, ffn, vocab, P):
     ses.decode_replay(0, 1)
     torch.cuda.synchronize()
     assert torch.equal(row, ses.logits[1])
+
+
+# Two sequences stepped in turn on two streams, nothing waited for between them: the one-kernel steps are put in order.
+def test_decode_steps_of_two_streams(S):
+    import torch
+    from paper_2403_00176_amd.session import DecoderSession
+    from workloads import configs
+    steps, lengths = 6, (126, 31)
+    w = configs.decoder(layers=2, hidden=512, heads=8, ffn=1024, vocab=1000, p_range=(1, 512), t_max=steps + 2, n_prompts=1)
+    weights = w.make_weights_by_name()
+    sessions = []
+    for P in lengths:
+        ses = DecoderSession(w.prefill, w.decode, w.t_max)
+        ses.upload_weights(weights)
+        ses.start(P, 1000)
+        ses.prefill(torch.from_numpy(np.random.RandomState(P).randint(0, 1000, P)).to(ses.device))
+        sessions.append(ses)
+    torch.cuda.synchronize()
+    assert sessions[0].stream != sessions[1].stream
+    for t in range(steps):
+        for ses in sessions:
+            ses.decode(t)
+    torch.cuda.synchronize()
+    together = [(s.logits.clone(), s.tokens.clone()) for s in sessions]
+    for ses, (logits, tokens) in zip(sessions, together):      # each on its own, the same tokens and bits
+        ses.logits[1:steps + 1].zero_()
+        torch.cuda.synchronize()
+        ses.decode_replay(0, steps)
+        torch.cuda.synchronize()
+        assert torch.equal(ses.logits[:steps + 1], logits[:steps + 1]) and torch.equal(ses.tokens, tokens)
