@@ -226,9 +226,9 @@ __global__ __launch_bounds__(LW * KG * 64, OCC * LW * KG / 4) void gemm_dl(AL al
   constexpr int EPI = NCW * 32 * ELD * 2;                       // wave-private fp32 patches, in bf16 units
   constexpr int RED = (KG - 1) * NCW * TM * TN * 16 * 64 * 2;   // the other groups' accumulators, in bf16 units
   constexpr int LDS_ELEMS = (ST * KG * STAGE > EPI + RED) ? ST * KG * STAGE : EPI + RED;
-  static_assert((NCW <= 2 || NCW == 4 || NCW == 8) && LW >= NCW && LW * KG <= 16 && TM >= 1 && TN >= 1 && LT >= 1 && ST >= 2 &&
+  static_assert((NCW == 4 || NCW == 8) && LW >= NCW && LW * KG <= 16 && TM >= 1 && TN >= 1 && LT >= 1 && ST >= 2 &&
                     (BM + BN) * KV % NT == 0 && BM % (64 / KV) == 0 && (KG == 1 || LW == NCW),
-                "1, 2, 4 or 8 compute waves per group, at most 16 waves");
+                "4 or 8 compute waves per group, at most 16 waves");
   static_assert((ST - 2) * LT <= 63, "vmcnt is a 6-bit counter");
   // behind the ring: FOLD 1 the tile's BN values of gamma; FOLD 2 per tile row (scale * rstd, -scale * rstd * mean),
   // then the tile's BN values of fold_s and of fold_c (staged here so that no register holds them through the k loop)
@@ -312,7 +312,7 @@ __global__ __launch_bounds__(LW * KG * 64, OCC * LW * KG / 4) void gemm_dl(AL al
   float2 sv[FOLD == 2 ? SL : 1];
   float s1 = 0.f, s2 = 0.f, m2 = 0.f;
   if (FOLD == 2) {
-    static_assert(FOLD != 2 || TPR == 2 || TPR == 4 || TPR == 8 || TPR == 16, "lanes of a row are neighbours within a row of 16 lanes");
+    static_assert(FOLD != 2 || TPR == 2 || TPR == 4 || TPR == 8, "lanes of a row are neighbours within a half row of lanes");
     const int P = g.K >> 5, row = m0 + tid / TPR, part = tid % TPR;
     const float2* pr = (const float2*)((const bf16_t*)g.A + (long long)g.M * g.K) + row;
     int j0 = part;
@@ -466,8 +466,7 @@ __global__ __launch_bounds__(LW * KG * 64, OCC * LW * KG / 4) void gemm_dl(AL al
   if (FOLD == 2) {                                              // the rows' statistics, for the epilogue
 #pragma unroll
     for (int u = 0; u < SL; ++u) { s1 += sv[u].x; s2 = fmaf(sv[u].x, sv[u].x, s2); m2 += sv[u].y; }
-    if (TPR == 16) { s1 = octet_sum(s1); s2 = octet_sum(s2); m2 = octet_sum(m2); s1 += dpp_move<0x128>(0.f, s1); s2 += dpp_move<0x128>(0.f, s2); m2 += dpp_move<0x128>(0.f, m2); }   // row_ror 8
-    else if (TPR == 8) { s1 = octet_sum(s1); s2 = octet_sum(s2); m2 = octet_sum(m2); }
+    if (TPR == 8) { s1 = octet_sum(s1); s2 = octet_sum(s2); m2 = octet_sum(m2); }
     else if (TPR == 4) { s1 = quad_sum(s1); s2 = quad_sum(s2); m2 = quad_sum(m2); }
     else { s1 = pair_sum(s1); s2 = pair_sum(s2); m2 = pair_sum(m2); }
     const float inv_k = 1.f / (float)g.K, mean = s1 * inv_k;
@@ -914,8 +913,6 @@ hipError_t launch_dl_variant(const AL& al, const GemmArgs& g, int tile, hipStrea
     case DL_128x128x64_S2_W8G2: return launch_dl<AL, 128, 128, 64, 2, 2, 4, 1, 8, 2>(al, g, s);
     case DL_128x128x64_S2_W8T: return launch_dl<AL, 128, 128, 64, 2, 4, 2, 2>(al, g, s);     // _T: 4 x 2 waves, a wave's rows are 128 bytes
     case DL_128x128x64_S3_W8T: return launch_dl<AL, 128, 128, 64, 3, 4, 2, 1>(al, g, s);
-    case DL_32x32x32_S4_G8: return launch_dl<AL, 32, 32, 32, 4, 1, 1, 1, 1, 8>(al, g, s);
-    case DL_64x32x32_S3_G8: return launch_dl<AL, 64, 32, 32, 3, 2, 1, 1, 2, 8>(al, g, s);
     default: return hipErrorInvalidValue;
   }
 }
@@ -939,8 +936,6 @@ static hipError_t launch_dl_fold(const DlMat& al, const GemmArgs& g, int tile, h
     case DL_256x256x64_S2_W8: return launch_dl<DlMat, 256, 256, 64, 2, 2, 4, 1, 8, 1, FOLD>(al, g, s);
     case DL_64x64x64_S3_G2: return launch_dl<DlMat, 64, 64, 64, 3, 2, 2, 1, 4, 2, FOLD>(al, g, s);
     case DL_64x64x64_S2_G2: return launch_dl<DlMat, 64, 64, 64, 2, 2, 2, 2, 4, 2, FOLD>(al, g, s);
-    case DL_32x32x32_S4_G8: return launch_dl<DlMat, 32, 32, 32, 4, 1, 1, 1, 1, 8, FOLD>(al, g, s);
-    case DL_64x32x32_S3_G8: return launch_dl<DlMat, 64, 32, 32, 3, 2, 1, 1, 2, 8, FOLD>(al, g, s);
     default: return hipErrorInvalidValue;                        // (the 16-wave tile with two k groups has no registers left for it)
   }
 }

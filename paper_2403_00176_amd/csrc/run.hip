@@ -483,8 +483,7 @@ struct Builder {
   static bool dl_can_fold(int variant) {
     switch (variant - V_DL0) {
       case DL_256x256x64_S2_W8: case DL_256x128x32_S3_W8: case DL_128x128x64_S3_W8T:
-      case DL_128x128x64_S2_W8T: case DL_64x64x64_S3_G2: case DL_64x64x64_S2_G2: case DL_64x64x64_S4_W4:
-      case DL_32x32x32_S4_G8: case DL_64x32x32_S3_G8: return true;
+      case DL_128x128x64_S2_W8T: case DL_64x64x64_S3_G2: case DL_64x64x64_S2_G2: case DL_64x64x64_S4_W4: return true;
       default: return false;
     }
   }

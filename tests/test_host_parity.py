@@ -141,6 +141,18 @@ def test_error_paths():
     assert S.sod2_binding_arena_bytes(S.sod2_bind(p4, {"L": 128}))[0] > 0   # undecided: plans every branch
 
 
+def test_forced_versions_are_the_built_ones():
+    w = configs.config2(1, layers=1)
+    g = S.sod2_graph_build(w.graph)
+    b = S.sod2_bind(S.sod2_plan(g, S.sod2_rdp_infer(g)), {"B": 1, "L": 32})
+    for v in [-1, 0, 6, 10, 34]:                  # automatic, the general kernels, the 25 tiles of the direct-to-LDS kernel
+        S.sod2_binding_force_variant(b, v)
+    for v in [-2, 7, 9, 35, 36]:
+        with pytest.raises(S.Sod2Error) as e:
+            S.sod2_binding_force_variant(b, v)
+        assert e.value.code == -1
+
+
 def test_tiny_fixture_graphs_match_oracle():
     from tests.test_oracle_rdp import _tiny_graphs
     for gd in _tiny_graphs():
