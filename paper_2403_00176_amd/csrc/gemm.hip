@@ -861,10 +861,11 @@ static QuickDiv quick_div(int d) {
   while ((1ll << l) < d) ++l;
   return {(uint32_t)(((1ull << 31) << l) / (unsigned)d + (d & (d - 1) ? 1 : 0)), (uint32_t)l};
 }
-// byte offsets within a tile (plus the row) and of a convolution's input stay below 2^31
+// byte offsets within a tile (plus the row) and of a convolution's input stay below 2^31 (a stride of 0, rows broadcast
+// by an Expand, is an offset like any other)
 bool dl_offsets_fit(const GemmArgs& g) {
   const long long lim = 0x7fffffffll;
-  return (256 * g.a_sm + g.K) * 2 < lim && (256 * g.b_sn + g.K) * 2 < lim && g.a_sm > 0 && g.b_sn > 0;
+  return (256 * g.a_sm + g.K) * 2 < lim && (256 * g.b_sn + g.K) * 2 < lim && g.a_sm >= 0 && g.b_sn >= 0;
 }
 
 template <class AL, int BM, int BN, int BK, int ST, int WM, int WN, int OCC, int LW = WM * WN, int KG = 1, int FOLD = 0>

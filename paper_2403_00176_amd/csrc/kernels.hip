@@ -1435,7 +1435,6 @@ static hipError_t launch_mfma_variant(const AL& al, const GemmArgs& g, int varia
 
 hipError_t launch_gemm_dl(const GemmArgs& g, int tile, hipStream_t s);
 hipError_t launch_conv_dl(const ConvArgs& c, const GemmArgs& g, int tile, hipStream_t s);
-bool dl_offsets_fit(const GemmArgs& g);
 
 hipError_t launch_gemv(const GemmArgs& g, hipStream_t s);
 hipError_t launch_gemm_ln(const GemmArgs& g, hipStream_t s);
@@ -1508,6 +1507,7 @@ hipError_t launch_gemm(const Launch& L, const GemmArgs& g, hipStream_t s) {
   if (L.variant == V_GEMV && L.in_dtype == SOD2_BF16_TAG && g.a_vec && g.b_mode == 0 && g.M <= 8) return launch_gemv(g, s);
   if (L.variant >= V_DL0 && L.in_dtype == SOD2_BF16_TAG && g.a_vec && g.b_mode == 0 && dl_offsets_fit(g))
     return launch_gemm_dl(g, L.variant - V_DL0, s);
+  if (g.fold) return hipErrorInvalidValue;                      // (no other kernel knows a folded LayerNorm)
   if (L.variant == V_SIMPLE || L.in_dtype != SOD2_BF16_TAG) {
     dim3 grid(((g.M + 63) / 64) * ((g.N + 63) / 64), g.nb0 * g.nb1);
     if (L.in_dtype == SOD2_BF16_TAG) hipLaunchKernelGGL(gemm_simple<bf16_t>, grid, dim3(256), 0, s, g);

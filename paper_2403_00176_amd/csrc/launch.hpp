@@ -59,6 +59,7 @@ struct GemmArgs {
   const void* fold_s;      // fold 2
   const void* fold_c;
 };
+bool dl_offsets_fit(const GemmArgs& g);   // the direct-to-LDS kernel can address the operands (gemm.hip)
 
 // Optional workspace behind the planned arena (fp32 partial tiles of split-K contractions)
 constexpr long long WS_PARTIAL_BYTES = 16 << 20;

@@ -510,11 +510,11 @@ struct Builder {
       const Epi ep = epilogue(gp), ec = epilogue(*gc);
       const bool prod = dl_can_fold(lp.variant) && a.nb0 * a.nb1 == 1 && a.c_sn == 1 && a.c_sm == a.N && a.N % 32 == 0 &&
                         a.a_sk == 1 && a.K % 8 == 0 && a.a_sm % 8 == 0 && a.b_sk == 1 && a.b_sn % 8 == 0 &&
-                        (ep.res < 0 || (a.r_sn == 1 && a.r_sm % 8 == 0));
+                        (ep.res < 0 || (a.r_sn == 1 && a.r_sm % 8 == 0)) && dl_offsets_fit(a);
       const bool cons = dl_can_fold(lc.variant) && c.splits == 1 && c.nb0 * c.nb1 == 1 && c.a_sk == 1 && c.a_sm == c.K &&
                         c.b_sk == 1 && c.b_sn % 8 == 0 && c.c_sn == 1 && c.c_sm % 8 == 0 && c.N % 8 == 0 &&
                         (ec.res < 0 || (c.r_sn == 1 && c.r_sm % 8 == 0)) && c.M == a.M && c.K == a.N &&
-                        (ec.bias < 0 || G.tensors[ec.bias].role == SOD2_WEIGHT) && p.const_off.count(gc->gid);
+                        (ec.bias < 0 || G.tensors[ec.bias].role == SOD2_WEIGHT) && dl_offsets_fit(c) && p.const_off.count(gc->gid);
       ok = prod && cons;
     }
     pair_memo[ln] = ok;

@@ -53,6 +53,52 @@ def test_fp32_contraction(S, M, N, K, trans_b, batch):
     assert got.shape == ref.shape and (np.abs(got - ref) <= bound).all(), np.max(np.abs(got - ref) / bound)
 
 
+# A contraction whose first operand repeats one row (an Expand: row stride 0), plain (with k split over workgroups) and
+# with the LayerNorm behind it folded into it and into the contraction that reads it.
+@pytest.mark.parametrize("M,K,folded", [(512, 256, True), (333, 768, True), (64, 4096, False)])
+def test_contraction_of_a_broadcast_row(S, M, K, folded):
+    import torch
+    from paper_2403_00176_amd.session import Session, to_host
+    from workloads import GraphBuilder
+    print(f"case M {M} K {K} folded {folded}", flush=True)
+    N, N2 = 512, 320
+    rs = np.random.RandomState(M + K)
+    bf = lambda *s: torch.from_numpy(rs.randn(*s).astype(np.float32)).bfloat16().double().numpy()  # noqa: E731
+    gb = GraphBuilder([("M", 1, 2048)])
+    x, like = gb.input("x", "bf16", [1, K]), gb.input("like", "bf16", ["M", K])
+    w, b = gb.weight("w", "bf16", [N, K]), gb.weight("b", "bf16", [N])
+    y = gb.op("Add", [gb.op("MatMul", [gb.op("Expand", [x, gb.op("Shape", [like], dtype="i64")]), w], transB=1), b])
+    X, W, B = bf(1, K), bf(N, K) / 16, bf(N)
+    weights, mid = {w: W, b: B}, X @ W.T + B
+    if folded:
+        gm, bt, w2 = gb.weight("gm", "bf16", [N]), gb.weight("bt", "bf16", [N]), gb.weight("w2", "bf16", [N2, N])
+        gb.mark_output(gb.op("MatMul", [gb.op("LayerNorm", [y, gm, bt], eps=1e-5), w2], transB=1), "z")
+        G, T, W2 = bf(N), bf(N), bf(N2, N) / 16
+        weights.update({gm: G, bt: T, w2: W2})
+        rstd = 1 / np.sqrt(mid.var() + 1e-5)
+        norm = (mid - mid.mean()) * rstd * G
+        ref = (norm + T) @ W2.T
+        # bf16 roundings on the way: the first result (which may also land on the neighbouring value), its product with
+        # the scale, the result; half an ulp is 2^-9 of the value
+        bound = (2.0 ** -8 + 2.0 ** -9) * (np.abs(mid * rstd * G) @ np.abs(W2.T)) + 2.0 ** -8 * (np.abs(ref) + np.abs(T) @ np.abs(W2.T))
+    else:
+        gb.mark_output(y, "z")
+        ref, bound = mid, 2.0 ** -8 * np.abs(mid) + 2.0 ** -18 * (np.abs(X) @ np.abs(W.T) + np.abs(B))
+    ses = Session(gb.build())
+    ses.upload_weights(weights)
+    bnd = ses.bind({"M": M})
+    outs = ses.alloc_outputs(ses.output_shapes(bnd))
+    arena = ses.ensure_arena(S.sod2_binding_arena_bytes(bnd)[0])
+    arena.fill_(0xff)                                          # (NaN wherever nothing is written)
+    ses.run(bnd, ses.upload_inputs({x: X, like: np.zeros((M, K))}), outs)
+    torch.cuda.synchronize()
+    trace = [e for e in S.sod2_run_trace(bnd) if e["is_group"]]
+    assert [e["fold"] for e in trace] == ([1, 2] if folded else [0])
+    assert folded or trace[0]["splits"] > 1
+    got = to_host(outs[0])
+    assert got.shape == (M, ref.shape[1]) and (np.abs(got - ref) <= bound).all(), np.max(np.abs(got - ref) / bound)
+
+
 # The decode step as one kernel against the same launches one by one: widths that deal out to 256, 192 and 128
 # workgroups, cache lengths at the edges of the parts of 128 keys an attention workgroup takes, one and many parts.
 @pytest.mark.parametrize("hidden,heads,ffn,vocab,P", [(512, 8, 1024, 1000, 126), (768, 12, 3072, 2002, 1), (1024, 16, 4096, 32000, 383),
