@@ -119,7 +119,6 @@ __device__ __forceinline__ uint32_t lds_addr(void* p) { return (uint32_t)uni((in
 __device__ __forceinline__ void wg_barrier() {
   asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
 }
-__device__ __forceinline__ float lane_f(float v, int l) { return __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(v), l)); }
 __device__ __forceinline__ float lo_f(uint32_t v) { return __uint_as_float(v << 16); }
 __device__ __forceinline__ float hi_f(uint32_t v) { return __uint_as_float(v & 0xffff0000u); }
 
@@ -290,31 +289,28 @@ __global__ __launch_bounds__(CH_THREADS, 4) void chain_kernel(ChainArgs a) {
 #pragma unroll
           for (int i = 0; i < 4; ++i) { g0[i] = lo_f(gm[i]); g1[i] = hi_f(gm[i]); b0[i] = lo_f(bt[i]); b1[i] = hi_f(bt[i]); }
           mail_wait<8>(a.mail, at, a.tag0 + src, v, &dead);
-          // sum and sum of squares in one round of lane moves; where the mean is so far from zero that their difference
-          // would lose digits (mean^2 > 64 var), once more around the mean
+          // the mean, then the squared distances from it, as the row kernels do it: a difference of two sums of squares
+          // would lose digits, and overflow for rows whose distances do not
           if (words < 512) {
 #pragma unroll
             for (int i = 0; i < 8; ++i) if (lane + 64 * i >= words) v[i] = 0u;
           }
-          float d[4] = {0.f, 0.f, 0.f, 0.f};
+          float d0 = 0.f, d1 = 0.f;
+#pragma unroll
+          for (int i = 0; i < 8; i += 2) {
+            d0 = dot2(v[i], 0x3f803f80u, d0);              // bf16 ones
+            d1 = dot2(v[i + 1], 0x3f803f80u, d1);
+          }
+          const float mean = wave_sum(d0 + d1) * inv_k;
+          d0 = d1 = 0.f;
 #pragma unroll
           for (int i = 0; i < 8; ++i) {
-            d[i & 1] = dot2(v[i], 0x3f803f80u, d[i & 1]);  // bf16 ones
-            d[2 + (i & 1)] = dot2(v[i], v[i], d[2 + (i & 1)]);
+            const bool in = words == 512 || lane + 64 * i < words;
+            const float a0 = in ? lo_f(v[i]) - mean : 0.f, a1 = in ? hi_f(v[i]) - mean : 0.f;
+            d0 = fmaf(a0, a0, d0);
+            d1 = fmaf(a1, a1, d1);
           }
-          d[0] += d[1];
-          d[1] = d[2] + d[3];
-          const float t = wave_sum4(d, lane);
-          const float mean = lane_f(t, 0) * inv_k;
-          float var = lane_f(t, 1) * inv_k - mean * mean;
-          if (__builtin_amdgcn_readfirstlane(mean * mean > 64.f * var)) {
-            float ss = 0.f;
-#pragma unroll
-            for (int i = 0; i < 8; ++i)
-              if (lane + 64 * i < words) { const float a0 = lo_f(v[i]) - mean, a1 = hi_f(v[i]) - mean; ss += a0 * a0 + a1 * a1; }
-            var = wave_sum(ss) * inv_k;
-          }
-          const float rstd = rsqrtf(var + eps);
+          const float rstd = rsqrtf(wave_sum(d0 + d1) * inv_k + eps);
           uint32_t u[4];
 #pragma unroll
           for (int i = 0; i < 4; ++i) u[i] = cw ? v[4 + i] : v[i];

@@ -152,6 +152,38 @@ def test_decode_step_as_one_kernel(S, hidden, heads, ffn, vocab, P):
     assert torch.equal(row, ses.logits[1])
 
 
+# Rows of nearly equal values whose squares overflow fp32 (1e19 and up) while the distances from their mean do not: the
+# LayerNorms of the one-kernel step take the variance from the distances, like those of the launches one by one.
+def test_decode_step_of_large_rows(S):
+    import torch
+    from paper_2403_00176_amd.session import DecoderSession
+    from workloads import configs
+    P, steps, vocab = 40, 3, 1000
+    w = configs.decoder(layers=2, hidden=512, heads=8, ffn=1024, vocab=vocab, p_range=(1, 512), t_max=steps + 2, n_prompts=1)
+    weights = w.make_weights_by_name()
+    rs = np.random.RandomState(7)
+    weights["tok_emb"] = 2.0 ** 64 * (1 + 2.0 ** -6 * rs.randint(0, 4, weights["tok_emb"].shape))
+    ses = DecoderSession(w.prefill, w.decode, w.t_max)
+    ses.upload_weights(weights)
+    ses.start(P, vocab)
+    ses.prefill(torch.from_numpy(rs.randint(0, vocab, P)).to(ses.device))
+    forced = torch.from_numpy(rs.randint(0, vocab, steps)).to(ses.device)
+    logits = []
+    for variant in (6, -1):
+        for t in range(steps):
+            with torch.cuda.stream(ses.stream):
+                ses.tokens[P + t] = forced[t]
+            b = ses.dec.bind({"P": P, "t": t})
+            S.sod2_binding_force_variant(b, variant)
+            ses.decode(t, b)
+        torch.cuda.synchronize()
+        logits.append(ses.logits[1:steps + 1].double())
+    a, b = logits
+    # the rows of tokens differ in their LayerNorm, so equal logits would mean that only its shift was left
+    assert torch.isfinite(a).all() and (a[0] - a[1]).norm() > 0.1 * a[0].norm()
+    assert ((a - b).norm() / a.norm()).item() <= 2 ** -8, ((a - b).norm() / a.norm()).item()
+
+
 # Two sequences stepped in turn on two streams, nothing waited for between them: the one-kernel steps are put in order.
 def test_decode_steps_of_two_streams(S):
     import torch
