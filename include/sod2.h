@@ -337,7 +337,8 @@ sod2_status sod2_run_exec_values(const sod2_binding_t*, int64_t* values_host, in
 /* What the last run did, step by step (Section 4.3: with control flow only the taken path is launched; Section
  * 4.4.2: the kernel version is picked at run time).  One entry per executed step: a group with the kernel family
  * (numbering of sod2_launch_record.kernel; -1 for a group whose result was empty), version and split-K count it was
- * launched with, or a control operator with the decision taken (Switch: 1 = the skip output, else -1). */
+ * launched with, or a control operator with the decision taken (Switch: 1 = the skip output, else -1).  kernel 23: the
+ * run was one kernel from end to end (a decode step: groups of one row each), this group a phase of it. */
 typedef struct {
   int32_t is_group;   /* 1 a group (ref = group id), 0 a Switch / Combine (ref = operator id) */
   int32_t ref;
@@ -354,7 +355,8 @@ sod2_status sod2_run_trace(const sod2_binding_t*, sod2_trace_entry* entries_host
 sod2_status sod2_run_plan_dump(const sod2_binding_t*, char* buf_host, size_t cap, size_t* needed);
 sod2_status sod2_run_arena_bytes(const sod2_binding_t*, size_t* arena_bytes, size_t* peak_live_bytes);
 
-/* per-launch records of the last run (filled when profiling is on: two events per launch).  The
+/* per-launch records of the last run (filled when profiling is on: two events per launch; every group is then a launch
+ * of its own, also where runs without profiling take one kernel for all of them).  The
  * first two records (kernel 7, groups -1 and -2) are one and two empty launches timed the same way:
  * twice the first minus the second is what the pair of events adds to every duration. */
 typedef struct {
@@ -389,8 +391,11 @@ sod2_status sod2_replay_create(const sod2_plan_t*, const int64_t* symbols_host, 
                                const void* const* inputs_dev, const int64_t* input_step_bytes_host, int32_t n_inputs,
                                void* const* outputs_dev, const int64_t* output_step_bytes_host, int32_t n_outputs,
                                int32_t* step_counter_dev, void* hip_stream, sod2_replay_t** out);
-/* enqueues: counter = first_step, then n_steps graph launches (each ends by advancing the counter) */
+/* enqueues n_steps steps, from first_step on, and leaves the counter behind the last one.  A step is one launch of the
+ * captured graph, or one kernel where its groups form a chain of one-row work (never on a stream under capture). */
 sod2_status sod2_replay_launch(sod2_replay_t*, int32_t first_step, int32_t n_steps, void* hip_stream);
+/* how the last sod2_replay_launch ran its steps: 1 each as one kernel, 0 as launches of the graph, -1 none yet */
+sod2_status sod2_replay_one_kernel(const sod2_replay_t*, int32_t* one_kernel);
 void sod2_replay_destroy(sod2_replay_t*);
 
 const char* sod2_last_error(void);

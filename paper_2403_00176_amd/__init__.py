@@ -37,7 +37,7 @@ EXPORTS = [
     "sod2_binding_force_splits", "sod2_binding_workspace_bytes",
     "sod2_plan_constants_bytes", "sod2_plan_prepare_constants", "sod2_binding_set_constants",
     "sod2_run", "sod2_run_static", "sod2_run_decisions", "sod2_run_exec_values", "sod2_run_plan_dump", "sod2_run_arena_bytes", "sod2_binding_set_profiling",
-    "sod2_binding_launch_records", "sod2_replay_create", "sod2_replay_launch", "sod2_replay_destroy",
+    "sod2_binding_launch_records", "sod2_replay_create", "sod2_replay_launch", "sod2_replay_one_kernel", "sod2_replay_destroy",
     "sod2_last_error", "sod2_version",
 ]
 
@@ -517,6 +517,13 @@ def sod2_replay_create(p: Plan, sym, step_symbol: str, max_steps: int, arena_ptr
 
 def sod2_replay_launch(r: Replay, first_step: int, n_steps: int, stream: int):
     _check(_lib.sod2_replay_launch(r.ptr, int(first_step), int(n_steps), C.c_void_p(stream)))
+
+
+def sod2_replay_one_kernel(r: Replay) -> Optional[bool]:
+    """Whether the last launch ran each step as one kernel; None before the first."""
+    v = C.c_int32()
+    _check(_lib.sod2_replay_one_kernel(r.ptr, C.byref(v)))
+    return None if v.value < 0 else bool(v.value)
 
 
 def sod2_version() -> str:

@@ -1741,6 +1741,7 @@ struct sod2_replay_s {
   std::vector<char*> ext;
   std::vector<int64_t> ext_step;
   int d_lk = 0;
+  int one_kernel = -1;                      // how the last launch ran its steps
   ~sod2_replay_s() {
     if (exec) (void)hipGraphExecDestroy(exec);
     if (graph) (void)hipGraphDestroy(graph);
@@ -1881,6 +1882,7 @@ extern "C" sod2_status sod2_replay_launch(sod2_replay_t* r, int32_t first_step, 
         chain_launch(r->chain, ext.data(), r->chain.lk0 + r->d_lk * i, s);
       }
       if (launch_step_set(r->step, first_step + n_steps, s) != hipSuccess) throw Error(SOD2_ERR_HIP, "step counter could not be set");
+      r->one_kernel = 1;
     } catch (const sod2::Error& e) {
       sod2::set_error(e.what());
       return e.code;
@@ -1893,6 +1895,12 @@ extern "C" sod2_status sod2_replay_launch(sod2_replay_t* r, int32_t first_step, 
   if (launch_step_set(r->step, first_step, s) != hipSuccess) { sod2::set_error("step counter could not be set"); return SOD2_ERR_HIP; }
   for (int i = 0; i < n_steps; ++i)
     if (hipGraphLaunch(r->exec, s) != hipSuccess) { sod2::set_error("graph launch failed"); return SOD2_ERR_HIP; }
+  r->one_kernel = 0;
+  return SOD2_OK;
+}
+extern "C" sod2_status sod2_replay_one_kernel(const sod2_replay_t* r, int32_t* one_kernel) {
+  if (!r || !one_kernel) { sod2::set_error("null argument"); return SOD2_ERR_INVALID_ARG; }
+  *one_kernel = r->one_kernel;
   return SOD2_OK;
 }
 extern "C" void sod2_replay_destroy(sod2_replay_t* r) { delete r; }
@@ -2043,7 +2051,7 @@ static sod2_status run_impl(sod2_binding_t* h, void* arena, size_t arena_bytes, 
           for (int i = 0; i < n_outputs; ++i) ext.push_back(outputs[i]);
           if (chain_fits(chain, ext.data())) {
             chain_launch(chain, ext.data(), chain.lk0, s);
-            for (size_t j = 0; j < h->b.steps.size(); ++j) trace_launch(h->launches[j], p.items[h->b.steps[j]].ref);
+            for (int at : h->b.steps) h->trace.push_back(sod2_trace_entry{1, p.items[at].ref, K_STEP, 0, 1, -1, 0});
             return SOD2_OK;
           }
         }

@@ -99,10 +99,21 @@ def test_contraction_of_a_broadcast_row(S, M, K, folded):
     assert got.shape == (M, ref.shape[1]) and (np.abs(got - ref) <= bound).all(), np.max(np.abs(got - ref) / bound)
 
 
-# The decode step as one kernel against the same launches one by one: widths that deal out to 256, 192 and 128
-# workgroups, cache lengths at the edges of the parts of 128 keys an attention workgroup takes, one and many parts.
+STEP = 23                                          # kernel of a trace entry: a phase of a step that ran as one kernel
+
+
+def ran_as_one_kernel(S, binding):
+    kernels = {e["kernel"] for e in S.sod2_run_trace(binding)}
+    assert kernels == {STEP} or STEP not in kernels
+    return kernels == {STEP}
+
+
+# The decode step as one kernel against the same launches one by one: widths whose rows deal out in whole pairs to 256,
+# 192, 256, 256, 192, 128 and 64 workgroups (of a chip with 256 CUs) and one, 640, that no number of them suits; cache
+# lengths at the edges of the parts of 128 keys an attention workgroup takes, one and many parts.
 @pytest.mark.parametrize("hidden,heads,ffn,vocab,P", [(512, 8, 1024, 1000, 126), (768, 12, 3072, 2002, 1), (1024, 16, 4096, 32000, 383),
-                                                      (512, 8, 2560, 998, 511), (768, 12, 1536, 5000, 250)])
+                                                      (512, 8, 2560, 998, 511), (768, 12, 1536, 5000, 250), (256, 4, 1024, 3000, 129),
+                                                      (128, 2, 512, 200, 300), (640, 10, 2560, 1000, 64)])
 def test_decode_step_as_one_kernel(S, hidden, heads, ffn, vocab, P):
     import torch
     from paper_2403_00176_amd.session import DecoderSession
@@ -125,6 +136,7 @@ def test_decode_step_as_one_kernel(S, hidden, heads, ffn, vocab, P):
             if one_by_one:
                 S.sod2_binding_force_variant(b, 6)
             ses.decode(t, b)
+            assert ran_as_one_kernel(S, b) == (not one_by_one and hidden != 640)
         torch.cuda.synchronize()
         d = w.decode
         caches = [ses.arena[at:at + (P + steps) * hidden * 2].view(torch.bfloat16).float().clone()
@@ -148,6 +160,7 @@ def test_decode_step_as_one_kernel(S, hidden, heads, ffn, vocab, P):
     torch.cuda.synchronize()
     row = ses.logits[1].clone()
     ses.decode_replay(0, 1)
+    assert S.sod2_replay_one_kernel(ses.replay) == (hidden != 640)
     torch.cuda.synchronize()
     assert torch.equal(row, ses.logits[1])
 
@@ -176,6 +189,7 @@ def test_decode_step_of_large_rows(S):
             b = ses.dec.bind({"P": P, "t": t})
             S.sod2_binding_force_variant(b, variant)
             ses.decode(t, b)
+            assert ran_as_one_kernel(S, b) == (variant == -1)
         torch.cuda.synchronize()
         logits.append(ses.logits[1:steps + 1].double())
     a, b = logits
@@ -203,7 +217,7 @@ def test_decode_steps_of_two_streams(S):
     assert sessions[0].stream != sessions[1].stream
     for t in range(steps):
         for ses in sessions:
-            ses.decode(t)
+            assert ran_as_one_kernel(S, ses.decode(t))
     torch.cuda.synchronize()
     together = [(s.logits.clone(), s.tokens.clone()) for s in sessions]
     for ses, (logits, tokens) in zip(sessions, together):      # each on its own, the same tokens and bits
