@@ -2037,7 +2037,7 @@ static sod2_status run_impl(sod2_binding_t* h, void* arena, size_t arena_bytes, 
 
     // One-row work from end to end (a decode step) runs as one kernel.  Not under capture: a replayed launch would carry
     // the tags of the captured one.
-    if (!static_ws && !ev && h->force_variant < 0 && p.opts.mvc && may_chain(p, h->b)) {
+    if (!static_ws && !ev && h->force_variant < 0 && h->force_splits == 0 && p.opts.mvc && may_chain(p, h->b)) {
       hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
       if (hipStreamIsCapturing(s, &capture) != hipSuccess) { (void)hipGetLastError(); capture = hipStreamCaptureStatusActive; }
       if (capture == hipStreamCaptureStatusNone) {

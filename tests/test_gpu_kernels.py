@@ -165,6 +165,25 @@ def test_decode_step_as_one_kernel(S, hidden, heads, ffn, vocab, P):
     assert torch.equal(row, ses.logits[1])
 
 
+# A binding that forces a version or a number of k ranges, or that is profiled, runs its groups one by one.
+def test_forced_and_profiled_decode_steps_run_group_by_group(S):
+    import torch
+    from paper_2403_00176_amd.session import DecoderSession
+    from workloads import configs
+    w = configs.decoder(layers=2, hidden=256, heads=4, ffn=512, vocab=200, p_range=(1, 512), t_max=4, n_prompts=1)
+    ses = DecoderSession(w.prefill, w.decode, w.t_max)
+    ses.upload_weights(w.make_weights_by_name())
+    ses.start(20, 200)
+    ses.prefill(torch.arange(20, device=ses.device))
+    for force, one in [(lambda b: None, True), (lambda b: S.sod2_binding_force_variant(b, 6), False),
+                       (lambda b: S.sod2_binding_force_splits(b, 2), False), (lambda b: S.sod2_binding_set_profiling(b, True), False)]:
+        b = ses.dec.bind({"P": 20, "t": 0})
+        force(b)
+        ses.decode(0, b)
+        assert ran_as_one_kernel(S, b) == one
+    torch.cuda.synchronize()
+
+
 # Rows of nearly equal values whose squares overflow fp32 (1e19 and up) while the distances from their mean do not: the
 # LayerNorms of the one-kernel step take the variance from the distances, like those of the launches one by one.
 def test_decode_step_of_large_rows(S):
