@@ -263,6 +263,13 @@ sod2_status sod2_binding_force_variant(sod2_binding_t*, int32_t variant);
 /* force the number of k ranges of every contraction that can split k (split-K: fp32 partial tiles
  * summed in a fixed order): 0 automatic, 1 never, n <= 16 that many where the workspace allows */
 sod2_status sod2_binding_force_splits(sod2_binding_t*, int32_t n);
+/* limits of the waits inside a run that is one kernel (a decode step: its workgroups exchange rows as they go), for tests
+ * of what happens past them; -1: the kernel's own.  arrive_us: how long the workgroups wait for one another to start;
+ * past it one of them does the whole run by itself, with the results of any other run, and the runs of the next 5 s are
+ * launched group by group.  polls: how often one then looks for a row of another; past it the row is NaN, and with it
+ * the results, an arg-max is -1, and the next run that would be one kernel returns SOD2_ERR_HIP, once; all further ones
+ * of the process are launched group by group. */
+sod2_status sod2_binding_force_waits(sod2_binding_t*, int32_t arrive_us, int32_t polls);
 /* Optional workspace.  When the arena handed to sod2_run is at least this many bytes longer than
  * sod2_binding_arena_bytes (rounded up to 256), its last workspace_bytes are used for split-K partial
  * sums; with a shorter arena no contraction splits k.  Either way the same call is bit-reproducible. */
@@ -303,7 +310,11 @@ sod2_status sod2_binding_set_constants(sod2_binding_t*, const void* constants_de
  * without Switch, NonZero and NMS only enqueue kernels and can be.  Kernel arguments are
  * prepared step by step while earlier kernels already execute: when a call fails (a group the
  * kernels do not support, an arena too small for the path taken) the groups before the failing one
- * may have run and the contents of the outputs and of the arena are unspecified. */
+ * may have run and the contents of the outputs and of the arena are unspecified.
+ * A graph whose executed groups form a chain of one-row work (a decode step) runs as one kernel, with sums in another
+ * order than the groups launched one by one; it takes the groups under capture, with a version or a number of k ranges
+ * forced, while profiled, on a stream with a CU mask, where a second process runs such graphs on the device, and for some
+ * seconds after its workgroups could not start together (see sod2_binding_force_waits). */
 sod2_status sod2_run(sod2_binding_t*, void* arena_dev, size_t arena_bytes,
                      const void* const* weights_dev, int32_t n_weights,
                      const void* const* inputs_dev, int32_t n_inputs,

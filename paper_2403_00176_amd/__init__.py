@@ -34,7 +34,7 @@ EXPORTS = [
     "sod2_plan_counts", "sod2_plan_dump", "sod2_plan_query_group", "sod2_bind", "sod2_bind_decided", "sod2_bind_executed",
     "sod2_binding_destroy",
     "sod2_binding_arena_bytes", "sod2_binding_dump", "sod2_binding_query_tensor", "sod2_run_query_tensor", "sod2_run_trace", "sod2_binding_force_decisions", "sod2_binding_force_variant",
-    "sod2_binding_force_splits", "sod2_binding_workspace_bytes",
+    "sod2_binding_force_splits", "sod2_binding_force_waits", "sod2_binding_workspace_bytes",
     "sod2_plan_constants_bytes", "sod2_plan_prepare_constants", "sod2_binding_set_constants",
     "sod2_run", "sod2_run_static", "sod2_run_decisions", "sod2_run_exec_values", "sod2_run_plan_dump", "sod2_run_arena_bytes", "sod2_binding_set_profiling",
     "sod2_binding_launch_records", "sod2_replay_create", "sod2_replay_launch", "sod2_replay_one_kernel", "sod2_replay_destroy",
@@ -347,6 +347,10 @@ def sod2_binding_force_decisions(b: Binding, decisions: Sequence[int]):
 
 def sod2_binding_force_variant(b: Binding, variant: int):
     _check(_lib.sod2_binding_force_variant(b.ptr, int(variant)))
+
+
+def sod2_binding_force_waits(b: Binding, arrive_us: int = -1, polls: int = -1):
+    _check(_lib.sod2_binding_force_waits(b.ptr, int(arrive_us), int(polls)))
 
 
 def sod2_binding_force_splits(b: Binding, n: int):

@@ -362,6 +362,12 @@ sod2_status sod2_binding_force_splits(sod2_binding_t* b, int32_t n) {
   b->launches_valid = false;
   return SOD2_OK;
 }
+sod2_status sod2_binding_force_waits(sod2_binding_t* b, int32_t arrive_us, int32_t polls) {
+  if (!b || arrive_us < -1 || arrive_us > 40000000 || polls < -1) { g_err = "limits must be -1 (the kernel's own) or up to 40 s and any number of polls"; return SOD2_ERR_INVALID_ARG; }
+  b->force_arrive_us = arrive_us;
+  b->force_polls = polls;
+  return SOD2_OK;
+}
 sod2_status sod2_binding_workspace_bytes(const sod2_binding_t* b, size_t* bytes) {
   if (!b || !bytes) { g_err = "null argument"; return SOD2_ERR_INVALID_ARG; }
   *bytes = (size_t)sod2::WS_BYTES;

@@ -15,11 +15,17 @@
 // v % nseg of 512 elements (one 16-byte load per lane and row), partial sums meet in LDS.  Attention: one workgroup per
 // head and 128 keys leaves its unnormalised sum, maximum and weight; the contraction behind it combines them as it reads.
 //
-// Waiting inside a kernel needs all workgroups on the chip at once, and one fills a CU.  The launcher lets one such
-// kernel at a time onto a device: an event orders launches of different streams, and of several processes on one device
-// only the first uses this kernel (it holds a socket name; the others launch group by group).  Other kernels come to an
-// end.  Every wait is bounded by the clock all the same: past the limit the kernel reports the failure to the host and
-// runs to its end without waiting.
+// Waiting inside a kernel needs all workgroups on the chip at once, and one fills a CU.  Nothing is assumed about that:
+// every workgroup counts itself in before it sends its first words, and whoever waits for those words longer than
+// CH_ARRIVE while some workgroup is missing calls the exchange off, in the word that holds the count, so that all agree.
+// Nothing but words has been written by then.  The workgroups leave, the ones that come later find the mark, and the
+// last of them computes the whole step by itself, with no one to wait for (10 ms instead of 0.4, but the same step);
+// the host then launches group by group for CH_REST seconds.  Once everyone has counted in, all are on the chip to the
+// end and no wait can be in vain; a limit of CH_POLLS polls stands against a broken machine: past it the row becomes NaN
+// (so do the logits; the token is -1) and the next step of the process reports the failure.
+// What keeps the workgroups from coming together for a while: kernels of other streams, streams whose CU mask is too
+// narrow (not given this kernel), a second process on the device.  Launches of different streams of this process are
+// ordered by an event, and of several processes that see each other's socket names only the first uses this kernel.
 //
 // One step of the 24-layer decoder (hidden 1024, FFN 4096, vocabulary 32000; 605 MB of weights) with 300 cached rows:
 // 0.87 ms as 124 kernels, 0.36 ms as this one (1.7 TB/s of weights).  A layer takes 14.6 us: per exchange 0.8 - 1.2 us
@@ -59,12 +65,20 @@ constexpr int CH_ATT = 80;                                                 // wo
 constexpr int CH_REGION = CHAIN_MAX_WG * CH_ATT;                           // words of one phase
 constexpr int CH_RING = 16;                                                // phases before a region is written again
 constexpr int CH_PART = 1024;                                              // partial sums of a phase in LDS
-constexpr unsigned long long CH_LIMIT = 1000000000ull;                     // 10 s of the 100 MHz clock
+constexpr int CH_ARRIVE = 20000;                                           // microseconds the workgroups wait for one another to start
+constexpr int CH_POLLS = 1 << 25;                                          // polls of one wait after that: upwards of 10 s
+constexpr int CH_REST = 5;                                                 // seconds without this kernel after a step done by one workgroup
+constexpr unsigned CH_OFF = 0x80000000u;                                   // in the count of arrivals: the exchange is off
+constexpr int CH_ROW = CHAIN_MAX_WG * CH_LINE;                             // words of a row (two bf16 each) of the lone workgroup
 
 struct ChainArgs {
   const ChainStep* steps;
   u64* mail;
-  unsigned* error;                  // pinned host word: set when a wait ran past its limit
+  unsigned* here;                   // arrivals of this launch
+  unsigned* here_next;              // of the next, cleared by this one
+  uint32_t* rows;                   // CH_RING rows of a workgroup that does the step by itself
+  unsigned* error;                  // pinned host words: [0] a wait ran past its limit, [1] a step was done by one workgroup
+  unsigned arrive, polls;           // limits of the waits: ticks of the 100 MHz clock, polls
   char* ext[CHAIN_MAX_EXT];         // the caller's inputs and outputs of this launch
   int n_steps, lk;
   unsigned tag0;
@@ -75,25 +89,41 @@ __device__ __forceinline__ void mail_store(u64* p, uint32_t payload, unsigned ta
   __hip_atomic_store(p, ((u64)tag << 32) | payload, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// the words at mail[at[0 .. n)] until all of them carry `tag`, or the limit has passed (*dead set).  (All n are asked for
-// together every time: a load under a condition of its own would be waited for on its own.)
+// the words at a.mail[at[0 .. n)] until all of them carry `tag`.  (All n are asked for together every time: a load under a
+// condition of its own would be waited for on its own.)  first: the wait for the first row, words of every workgroup,
+// which may not all be on the chip; *left is set when the exchange is off.  Past the limit of polls (*dead set) the words
+// are NaN, of either type.
 template <int n>
-__device__ __forceinline__ void mail_wait(const u64* mail, const uint32_t (&at)[n], unsigned tag, uint32_t (&v)[n], int* dead) {
+__device__ __forceinline__ void mail_wait(const ChainArgs& a, const uint32_t (&at)[n], unsigned tag, uint32_t (&v)[n], int* dead, bool first, int* left) {
   u64 w[n];
   unsigned spins = 0;
   u64 t0 = 0;
   for (;;) {
     bool all = true;
 #pragma unroll
-    for (int i = 0; i < n; ++i) w[i] = mail_load(mail + at[i]);
+    for (int i = 0; i < n; ++i) w[i] = mail_load(a.mail + at[i]);
 #pragma unroll
     for (int i = 0; i < n; ++i) all = all && (unsigned)(w[i] >> 32) == tag;
     if (all) break;
-    if ((++spins & 255) == 0) {
-      const u64 now = wall_clock64();
-      if (t0 == 0) t0 = now;
-      if (now - t0 > CH_LIMIT || __hip_atomic_load(dead, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)) {
+    if ((++spins & 255) == 0 || spins >= a.polls) {
+      if (first) {
+        unsigned here = __hip_atomic_load(a.here, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (here < gridDim.x) {                            // (someone is missing, and the exchange is on)
+          const u64 now = wall_clock64();
+          if (t0 == 0) t0 = now;
+          if (now - t0 < a.arrive) continue;
+          if (!__hip_atomic_compare_exchange_strong(a.here, &here, here | CH_OFF, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) continue;
+          here |= CH_OFF;
+        }
+        if (here & CH_OFF) {
+          __hip_atomic_store(left, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+          break;
+        }
+      }
+      if (spins >= a.polls || __hip_atomic_load(dead, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)) {
         __hip_atomic_store(dead, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+#pragma unroll
+        for (int i = 0; i < n; ++i) w[i] = 0x7fc07fc0u;
         break;
       }
     }
@@ -154,9 +184,156 @@ __device__ __forceinline__ void wave_argmax(float& v, int& i) {
   }
 }
 
+// The whole step by one workgroup that waits for no other: 16 waves, a pair of rows or a head to a wave at a time.  Rows
+// lie in a.rows, two values to a word; the values are those the exchanged rows would hold (sums in another order).
+__device__ __forceinline__ void step_alone(const ChainArgs& a, const ChainStep* steps, char* const* ext, uint32_t* xw, float* part) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = uni(tid >> 6);
+  constexpr int WAVES = CH_THREADS / 64;
+  auto row_of = [&](int p) __attribute__((always_inline)) { return a.rows + (p & (CH_RING - 1)) * CH_ROW; };
+  for (int p = 0; p < a.n_steps; ++p) {
+    const ChainStep& s = steps[p];
+    const int kind = uni(s.kind), n = uni(s.n);
+    uint32_t* out = row_of(p);
+    const uint32_t* in = row_of(uni(s.src));               // (a first phase has none and reads none)
+    if (kind == CHAIN_GATHER) {
+      auto row = [&](const void* table, int slot, long long rows, int i32) {
+        const char* ix = ext[slot];
+        long long id = i32 ? (long long)*(const int*)ix : *(const long long*)ix;
+        id = id < 0 ? 0 : (id >= rows ? rows - 1 : id);
+        return (const uint32_t*)((const bf16_t*)table + id * n);
+      };
+      for (int i = tid; i < n / 2; i += CH_THREADS) {
+        uint32_t v = row(s.w, s.idx_ext, s.table_rows, s.idx_i32)[i];
+        if (s.bias) {
+          const uint32_t u = row(s.bias, s.idx2_ext, s.table2_rows, s.idx2_i32)[i];
+          v = f2bf2(lo_f(v) + lo_f(u), hi_f(v) + hi_f(u));
+        }
+        out[i] = v;
+      }
+    } else if (kind == CHAIN_ATTN) {
+      const int lk = a.lk + uni(s.lk_rel), ldw = uni(s.ldw), kg = lane >> 3, dc = lane & 7;
+      const float scale = __uint_as_float(uni(__float_as_uint(s.scale))) * 1.4426950408889634f;
+      for (int h = wave; h < n; h += WAVES) {
+        const int col = h * 64 + dc * 8;
+        u32x4 q, kn, vn;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          q[e] = in[((s.q_off + col) >> 1) + e];
+          kn[e] = in[((s.k_off + col) >> 1) + e];
+          vn[e] = in[((s.v_off + col) >> 1) + e];
+        }
+        float m = -INFINITY, l = 0.f, o[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+        for (int t0 = 0; t0 < lk; t0 += 8) {
+          const int t = t0 + kg;
+          u32x4 kr = kn, vr = vn;
+          if (t < lk - 1) {
+            kr = *(const u32x4*)((const bf16_t*)s.w + (long long)t * ldw + col);
+            vr = *(const u32x4*)((const bf16_t*)s.bias + (long long)t * ldw + col);
+          }
+          float d = 0.f;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) d = dot2(q[e], kr[e], d);
+          d = octet_sum(d) * scale;
+          if (t < lk) {
+            const float mn = fmaxf(m, d), f = m == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m - mn);
+            const float pr = d == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(d - mn);
+            l = fmaf(l, f, pr);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+              o[2 * e] = fmaf(o[2 * e], f, pr * lo_f(vr[e]));
+              o[2 * e + 1] = fmaf(o[2 * e + 1], f, pr * hi_f(vr[e]));
+            }
+            m = mn;
+          }
+        }
+        const float mx = wave_max(m), f = m == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m - mx);
+        l *= f;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) o[e] *= f;
+#pragma unroll
+        for (int x = 8; x < 64; x <<= 1) {
+          l += __shfl_xor(l, x, 64);
+#pragma unroll
+          for (int e = 0; e < 8; ++e) o[e] += __shfl_xor(o[e], x, 64);
+        }
+        if (kg == 0) {
+          const float inv = 1.f / l;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) out[(col >> 1) + e] = f2bf2(o[2 * e] * inv, o[2 * e + 1] * inv);
+          *(u32x4*)((bf16_t*)s.w + (long long)(lk - 1) * ldw + col) = kn;       // the cache rows for later steps
+          *(u32x4*)((bf16_t*)s.bias + (long long)(lk - 1) * ldw + col) = vn;
+        }
+      }
+    } else {
+      const int K = uni(s.k), words = K >> 1, ldw = uni(s.ldw), act1 = uni(s.act1), act2 = uni(s.act2), res = uni(s.res);
+      if (s.gamma) {                                       // (K <= 1024: word 64 i + lane of the row, waves 0 .. 7 write one each)
+        float d0 = 0.f;
+        uint32_t v[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+          v[i] = lane + 64 * i < words ? in[lane + 64 * i] : 0u;
+          d0 += lo_f(v[i]) + hi_f(v[i]);
+        }
+        const float inv_k = 1.f / (float)K, mean = wave_sum(d0) * inv_k;
+        d0 = 0.f;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+          const bool on = lane + 64 * i < words;
+          const float a0 = on ? lo_f(v[i]) - mean : 0.f, a1 = on ? hi_f(v[i]) - mean : 0.f;
+          d0 = fmaf(a0, a0, fmaf(a1, a1, d0));
+        }
+        const float rstd = rsqrtf(wave_sum(d0) * inv_k + s.eps);
+        const int i = wave * 64 + lane;
+        if (i < words) {
+          const uint32_t x = in[i], g = ((const uint32_t*)s.gamma)[i], b = ((const uint32_t*)s.beta)[i];
+          xw[i] = f2bf2(fmaf((lo_f(x) - mean) * rstd, lo_f(g), lo_f(b)), fmaf((hi_f(x) - mean) * rstd, hi_f(g), hi_f(b)));
+        }
+      } else {
+        for (int i = tid; i < words; i += CH_THREADS) xw[i] = in[i];
+      }
+      __syncthreads();
+      float bv = -INFINITY;
+      int bi = 0x7fffffff;
+      for (int i = wave; 2 * i < n; i += WAVES) {
+        const bf16_t* w = (const bf16_t*)s.w + 2ll * i * ldw;
+        float d0 = 0.f, d1 = 0.f;
+        for (int k = lane * 8; k < K; k += 512) {
+          const u32x4 x = *(const u32x4*)&xw[k >> 1], w0 = *(const u32x4*)(w + k), w1 = *(const u32x4*)(w + ldw + k);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) { d0 = dot2(x[e], w0[e], d0); d1 = dot2(x[e], w1[e], d1); }
+        }
+        const uint32_t b2 = s.bias ? ((const uint32_t*)s.bias)[i] : 0u;
+        float v0 = apply_act(wave_sum(d0) * s.scale + lo_f(b2), act1), v1 = apply_act(wave_sum(d1) * s.scale + hi_f(b2), act1);
+        if (res >= 0) {
+          const uint32_t r = row_of(res)[i];
+          v0 = apply_act(v0 + lo_f(r), act2);
+          v1 = apply_act(v1 + hi_f(r), act2);
+        }
+        const uint32_t o = f2bf2(v0, v1);
+        if (lane == 0) (s.out_ext >= 0 ? (uint32_t*)ext[s.out_ext] : out)[i] = o;
+        if (bi == 0x7fffffff || lo_f(o) > bv) { bv = lo_f(o); bi = 2 * i; }
+        if (hi_f(o) > bv) { bv = hi_f(o); bi = 2 * i + 1; }
+      }
+      if (s.arg_ext >= 0) {
+        int* index = (int*)(part + WAVES);
+        if (lane == 0) { part[wave] = bv; index[wave] = bi; }
+        __syncthreads();
+        if (tid == 0) {
+          for (int v = 1; v < WAVES; ++v)
+            if (index[v] != 0x7fffffff && (bi == 0x7fffffff || part[v] > bv || (part[v] == bv && index[v] < bi))) { bv = part[v]; bi = index[v]; }
+          if (s.arg_i32) *(int*)ext[s.arg_ext] = bi;
+          else *(long long*)ext[s.arg_ext] = bi;
+        }
+      }
+    }
+    __syncthreads();                                       // the row is there for everyone, and xw free
+  }
+  if (tid == 0) __hip_atomic_store(a.error + 1, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 // The waves of a workgroup have one of two parts, because a wave's loads come back in order: a wave that polls must not
-// have weights on their way.  Waves 8 .. 15 gather, wait for rows and leave them (normalised) in LDS; waves 0 .. 7 hold
-// the weights of two phases in registers, multiply, and wave 0 finishes and sends the rows.  Two barriers per phase:
+// have weights on their way.  Waves 8 .. 15 gather, wait for rows and leave them (normalised) in LDS; waves 0 .. 7 keep
+// the weights of two phases on their way into a ring of LDS, multiply, and wave 0 finishes and sends the rows.  Two barriers per phase:
 // row there, partial sums there.
 __global__ __launch_bounds__(CH_THREADS, 4) void chain_kernel(ChainArgs a) {
   __shared__ ChainStep steps[CHAIN_MAX_STEPS];
@@ -169,17 +346,25 @@ __global__ __launch_bounds__(CH_THREADS, 4) void chain_kernel(ChainArgs a) {
   __shared__ __attribute__((aligned(16))) uint32_t qkv[96];                // attention: the head's query, new key, new value
   __shared__ float am[CH_WAVES], al[CH_WAVES], ao[CH_WAVES][64];
   __shared__ uint32_t nowhere[64];
-  __shared__ int dead;
+  __shared__ int dead, left;                               // a wait ran past its limit; the exchange is off
+  __shared__ unsigned arrived;
   __shared__ char* ext[CHAIN_MAX_EXT];
   const int tid = threadIdx.x, lane = tid & 63, wave = uni(tid >> 6);
   const int wg = blockIdx.x, nwg = gridDim.x;
   for (int i = tid; i < a.n_steps * (int)(sizeof(ChainStep) / 16); i += CH_THREADS) ((uint4*)steps)[i] = ((const uint4*)a.steps)[i];
   if (tid == 0) {
-    dead = 0;
+    dead = left = 0;
+    if (a.arrive == 0) __hip_atomic_fetch_or(a.here, CH_OFF, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    arrived = __hip_atomic_fetch_add(a.here, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (wg == 0) __hip_atomic_store(a.here_next, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 #pragma unroll
     for (int i = 0; i < CHAIN_MAX_EXT; ++i) ext[i] = a.ext[i];
   }
   __syncthreads();
+  if (uni((int)arrived) < 0) {                             // the exchange is off: the last one to come does the step
+    if ((uni((int)arrived) & 0x7fffffff) == nwg - 1) step_alone(a, steps, ext, xw, part);
+    return;
+  }
 
   // attention: parts per head; part head * splits + split of this workgroup, or -1
   auto attn_splits = [&](const ChainStep& s) __attribute__((always_inline)) { return (a.lk + uni(s.lk_rel) + CHAIN_KEYS - 1) / CHAIN_KEYS; };
@@ -230,7 +415,7 @@ __global__ __launch_bounds__(CH_THREADS, 4) void chain_kernel(ChainArgs a) {
           const int which = ct >> 5, off = which == 0 ? s.q_off : (which == 1 ? s.k_off : s.v_off);
           uint32_t at[1] = {word_of(src, ((off + h * 64) >> 1) + (ct & 31))};
           uint32_t v[1];
-          mail_wait<1>(a.mail, at, a.tag0 + src, v, &dead);
+          mail_wait<1>(a, at, a.tag0 + src, v, &dead, false, &left);
           qkv[ct] = v[0];
         }
         wg_barrier();
@@ -253,7 +438,7 @@ __global__ __launch_bounds__(CH_THREADS, 4) void chain_kernel(ChainArgs a) {
               const uint32_t b = base + min(s0 + u, splits - 1) * CH_ATT;
               at[4 * u] = b + e; at[4 * u + 1] = b + e + 1; at[4 * u + 2] = b + 64; at[4 * u + 3] = b + 65;
             }
-            mail_wait<16>(a.mail, at, a.tag0 + src, v, &dead);
+            mail_wait<16>(a, at, a.tag0 + src, v, &dead, false, &left);
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
               if (s0 + u >= splits) continue;
@@ -288,7 +473,7 @@ __global__ __launch_bounds__(CH_THREADS, 4) void chain_kernel(ChainArgs a) {
           float g0[4], g1[4], b0[4], b1[4];
 #pragma unroll
           for (int i = 0; i < 4; ++i) { g0[i] = lo_f(gm[i]); g1[i] = hi_f(gm[i]); b0[i] = lo_f(bt[i]); b1[i] = hi_f(bt[i]); }
-          mail_wait<8>(a.mail, at, a.tag0 + src, v, &dead);
+          mail_wait<8>(a, at, a.tag0 + src, v, &dead, p == 1, &left);
           // the mean, then the squared distances from it, as the row kernels do it: a difference of two sums of squares
           // would lose digits, and overflow for rows whose distances do not
           if (words < 512) {
@@ -323,13 +508,14 @@ __global__ __launch_bounds__(CH_THREADS, 4) void chain_kernel(ChainArgs a) {
         uint32_t at[PER], v[PER];
 #pragma unroll
         for (int i = 0; i < PER; ++i) at[i] = word_of(src, min(ct + i * CH_IN * 64, words - 1));
-        mail_wait<PER>(a.mail, at, a.tag0 + src, v, &dead);
+        mail_wait<PER>(a, at, a.tag0 + src, v, &dead, p == 1, &left);
 #pragma unroll
         for (int i = 0; i < PER; ++i) if (ct + i * CH_IN * 64 < words) xw[ct + i * CH_IN * 64] = v[i];
       }
       const int rpw = uni(s.rpw);
       wg_barrier();
       wg_barrier();
+      if (p == 1 && uni(left)) break;
       if (uni(s.arg_ext) >= 0 && wg == 0 && cw == 0) {
         // arg-max: every workgroup's best pair
         float bv = -INFINITY;
@@ -339,12 +525,13 @@ __global__ __launch_bounds__(CH_THREADS, 4) void chain_kernel(ChainArgs a) {
           const uint32_t line = region(p) + i / waves * CH_LINE + i % waves * 2;
           uint32_t at[2] = {line, line + 1};
           uint32_t v[2];
-          mail_wait<2>(a.mail, at, a.tag0 + p, v, &dead);
+          mail_wait<2>(a, at, a.tag0 + p, v, &dead, false, &left);
           const float ov = __uint_as_float(v[0]);
           const int oi = (int)v[1];
           if (oi != 0x7fffffff && (bi == 0x7fffffff || ov > bv || (ov == bv && oi < bi))) { bv = ov; bi = oi; }
         }
         wave_argmax(bv, bi);
+        if (__hip_atomic_load(&dead, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)) bi = -1;
         if (lane == 0) {
           if (s.arg_i32) *(int*)ext[s.arg_ext] = bi;
           else *(long long*)ext[s.arg_ext] = bi;
@@ -532,7 +719,7 @@ __global__ __launch_bounds__(CH_THREADS, 4) void chain_kernel(ChainArgs a) {
       const float scale = __uint_as_float(uni(__float_as_uint(s.scale)));
       const int k = (wave & ((1 << sh) - 1)) * 512 + lane * 8, row0 = wg * rpw + 2 * tid;
       const bool mine = 2 * tid < rpw && row0 < n;
-            wg_barrier();
+      wg_barrier();
       u32x4 xv = *(const u32x4*)&xw[min(k, K - 8) >> 1];
       issue(next, p + CH_AHEAD);
       if (k >= K) xv = zero;
@@ -620,7 +807,10 @@ __global__ __launch_bounds__(CH_THREADS, 4) void chain_kernel(ChainArgs a) {
     }
 #pragma unroll
     for (int p = 0; p < CH_AHEAD; ++p) issue(plan(p), p);
-    for (int p = 0; p < n_steps; ++p) phase(p);
+    for (int p = 0; p < n_steps; ++p) {
+      phase(p);
+      if (p == 1 && uni(left)) break;                      // (words of a row that nobody reads have gone out, nothing else)
+    }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");       // nothing of the ring is on its way when the workgroup ends
   }
   wg_barrier();
@@ -643,15 +833,21 @@ __global__ __launch_bounds__(256) void chain_clear_kernel(u64* mail, long long n
 constexpr int CH_TABLES = 8;
 static __device__ __align__(256) u64 chain_mail[CH_RING * CH_REGION];
 static __device__ __align__(256) ChainStep chain_tables[CH_TABLES][CHAIN_MAX_STEPS];
+static __device__ __align__(256) unsigned chain_here[2][64];               // arrivals of this launch and the next
+static __device__ __align__(256) uint32_t chain_rows[CH_RING * CH_ROW];
 
 namespace {
 struct ChainDevice {
   std::mutex mu;
   bool known = false;
   int n_cu = 0, owner = -1;                 // owner: the socket that holds the device's name, or -1
-  std::chrono::steady_clock::time_point asked;
+  std::chrono::steady_clock::time_point asked, again;      // asked for the name; when this kernel may be used again
+  bool failed = false;
   u64* mail = nullptr;
   ChainStep* tables = nullptr;
+  unsigned* here = nullptr;
+  uint32_t* rows = nullptr;
+  int turn = 0;                             // which count of arrivals the next launch takes
   unsigned* err_host = nullptr;
   unsigned* err_dev = nullptr;
   hipEvent_t last = nullptr;                // recorded behind the newest launch
@@ -680,16 +876,22 @@ void first_use(ChainDevice& d) {
   d.mail = (u64*)p;
   need(hipGetSymbolAddress(&p, HIP_SYMBOL(chain_tables)), "address of the step tables");
   d.tables = (ChainStep*)p;
+  need(hipGetSymbolAddress(&p, HIP_SYMBOL(chain_here)), "address of the counts of arrivals");
+  d.here = (unsigned*)p;
+  need(hipGetSymbolAddress(&p, HIP_SYMBOL(chain_rows)), "address of the lone workgroup's rows");
+  d.rows = (uint32_t*)p;
   need(hipHostMalloc((void**)&d.err_host, 64, hipHostMallocCoherent | hipHostMallocMapped), "pinned host memory");
   need(hipHostGetDevicePointer((void**)&d.err_dev, d.err_host, 0), "pinned host memory");
-  *d.err_host = 0;
+  d.err_host[0] = d.err_host[1] = 0;
   need(hipEventCreateWithFlags(&d.last, hipEventDisableTiming), "event");
   d.known = true;
 }
 }  // namespace
 
 // Whether this process may run one-row steps as one kernel on the current device: it holds an abstract socket name (no
-// file, gone with the process).  Asked again once a second while another process has it.
+// file, gone with the process).  Asked again once a second while another process has it.  (Processes in different
+// network namespaces do not see each other's names: their steps then meet, are called off and done by one workgroup, and
+// both go on group by group for a while.)
 static bool own_device(ChainDevice& d) {
   if (d.owner >= 0) return true;
   const auto now = std::chrono::steady_clock::now();
@@ -712,13 +914,30 @@ static bool own_device(ChainDevice& d) {
   return true;
 }
 
-// workgroups a one-row step may have on the current device: one per CU, 0 where another process runs such steps
-int chain_workgroups() {
+// a stream that may use only some of the CUs
+static bool masked(hipStream_t s, int n_cu) {
+  uint32_t mask[32] = {0};
+  if (hipExtStreamGetCUMask(s, 32, mask) != hipSuccess) { (void)hipGetLastError(); return false; }
+  int bits = 0;
+  for (uint32_t m : mask) bits += __builtin_popcount(m);
+  return bits > 0 && bits < n_cu;
+}
+
+// Workgroups a one-row step may have on stream s: one per CU, 0 where it is to be launched group by group.  Throws once
+// if an earlier step could not be brought to its end.
+int chain_workgroups(hipStream_t s) {
   ChainDevice& d = chain_device();
   std::lock_guard<std::mutex> lock(d.mu);
-  if (!own_device(d)) return 0;
+  if (d.failed || !own_device(d)) return 0;
   first_use(d);
-  return d.n_cu;
+  if (__atomic_load_n(&d.err_host[0], __ATOMIC_RELAXED)) {
+    d.failed = true;
+    throw Error(SOD2_ERR_HIP, "an earlier one-row step waited too long for another workgroup: its logits are NaN, and what was computed from them "
+                              "is not valid; such steps run group by group from now on");
+  }
+  const auto now = std::chrono::steady_clock::now();
+  if (__atomic_exchange_n(&d.err_host[1], 0u, __ATOMIC_RELAXED)) d.again = now + std::chrono::seconds(CH_REST);
+  return now < d.again || masked(s, d.n_cu) ? 0 : d.n_cu;
 }
 
 // One step on stream s.  ext: the caller's input and output pointers; lk: keys of the attention phases with lk_rel 0.
@@ -726,8 +945,6 @@ void chain_launch(const Chain& c, void* const* ext, int lk, hipStream_t s) {
   ChainDevice& d = chain_device();
   std::lock_guard<std::mutex> lock(d.mu);
   first_use(d);
-  if (__atomic_load_n(d.err_host, __ATOMIC_RELAXED))
-    throw Error(SOD2_ERR_HIP, "a one-row step waited too long for another workgroup: its results and what was computed from them are not valid");
   // on the same stream too: a handle may by now be another stream's (destroyed and created again, or the per-thread one)
   if (d.any) need(hipStreamWaitEvent(s, d.last, 0), "ordering one-row steps of two streams");
   int slot = -1, oldest = 0;
@@ -756,7 +973,12 @@ void chain_launch(const Chain& c, void* const* ext, int lk, hipStream_t s) {
   ChainArgs a;
   a.steps = d.tables + (size_t)slot * CHAIN_MAX_STEPS;
   a.mail = d.mail;
+  a.here = d.here + 64 * d.turn;
+  a.here_next = d.here + 64 * (d.turn ^ 1);
+  a.rows = d.rows;
   a.error = d.err_dev;
+  a.arrive = 100u * (unsigned)(c.arrive_us >= 0 ? c.arrive_us : CH_ARRIVE);
+  a.polls = (unsigned)(c.polls >= 0 ? c.polls : CH_POLLS);
   for (int i = 0; i < CHAIN_MAX_EXT; ++i) a.ext[i] = i < c.n_ext ? (char*)ext[i] : nullptr;
   a.n_steps = (int)c.steps.size();
   a.lk = lk;
@@ -764,6 +986,7 @@ void chain_launch(const Chain& c, void* const* ext, int lk, hipStream_t s) {
   d.next_tag += (unsigned)c.steps.size();
   hipLaunchKernelGGL(chain_kernel, dim3(c.workgroups), dim3(CH_THREADS), 0, s, a);
   need(hipGetLastError(), "one-row step");
+  d.turn ^= 1;                              // (a launch that failed has counted nobody in)
   need(hipEventRecord(d.last, s), "one-row step");
   d.any = true;
 }

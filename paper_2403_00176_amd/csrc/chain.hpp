@@ -32,9 +32,10 @@ struct alignas(16) ChainStep {
 struct Chain {
   std::vector<ChainStep> steps;
   int workgroups = 0, n_ext = 0, lk0 = 0;
+  int arrive_us = -1, polls = -1;      // limits of the waits between its workgroups, -1: the kernel's own
 };
 
-int chain_workgroups();
+int chain_workgroups(hipStream_t s);
 bool chain_build(const std::vector<Launch>& launches, int n_in, int n_out, const std::function<void*(const Ref&)>& at, int n_cu, int lk_grows,
                  Chain* out);
 bool chain_fits(const Chain& c, void* const* ext);

@@ -17,6 +17,7 @@ struct sod2_binding_s {
   bool has_forced = false;
   int force_variant = -1;
   int force_splits = 0;                     // 0 automatic, 1 never split k, n > 1 that many k ranges where possible
+  int force_arrive_us = -1, force_polls = -1;   // limits of the waits inside a one-kernel step, -1 its own
   bool profiling = false;
   const void* constants = nullptr;          // constants derived from the weights (folded LayerNorms), or null: not folded
   size_t constants_bytes = 0;

@@ -1831,7 +1831,7 @@ extern "C" sod2_status sod2_replay_create(const sod2_plan_t* ph, const int64_t* 
         if (r->d_lk == 0) r->d_lk = L.d_lk;
         same_growth = same_growth && L.d_lk == r->d_lk;
       }
-    if (same_growth && chain_build(L0, n_inputs, n_outputs, [&](const Ref& ref) { return P.at(ref); }, chain_workgroups(),
+    if (same_growth && chain_build(L0, n_inputs, n_outputs, [&](const Ref& ref) { return P.at(ref); }, chain_workgroups(s),
                                    r->d_lk * (max_steps - 1), &r->chain)) {
       for (int i = 0; i < n_inputs; ++i) { r->ext.push_back((char*)inputs[i]); r->ext_step.push_back(P.in_step[i]); }
       for (int i = 0; i < n_outputs; ++i) { r->ext.push_back((char*)outputs[i]); r->ext_step.push_back(P.out_step[i]); }
@@ -1868,14 +1868,10 @@ extern "C" sod2_status sod2_replay_launch(sod2_replay_t* r, int32_t first_step, 
   }
   hipStream_t s = (hipStream_t)stream;
   // one kernel per step, but not under capture: a captured launch run again would carry the tags of its first run
-  bool chained = r->chained;
-  if (chained) {
+  try {
     hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(s, &capture) != hipSuccess) { (void)hipGetLastError(); capture = hipStreamCaptureStatusActive; }
-    chained = capture == hipStreamCaptureStatusNone;
-  }
-  if (chained) {
-    try {
+    if (r->chained && hipStreamIsCapturing(s, &capture) != hipSuccess) { (void)hipGetLastError(); capture = hipStreamCaptureStatusActive; }
+    if (r->chained && capture == hipStreamCaptureStatusNone && chain_workgroups(s) >= r->chain.workgroups) {
       std::vector<void*> ext(r->ext.size());
       for (int i = first_step; i < first_step + n_steps; ++i) {
         for (size_t k = 0; k < ext.size(); ++k) ext[k] = r->ext[k] + r->ext_step[k] * i;
@@ -1883,14 +1879,14 @@ extern "C" sod2_status sod2_replay_launch(sod2_replay_t* r, int32_t first_step, 
       }
       if (launch_step_set(r->step, first_step + n_steps, s) != hipSuccess) throw Error(SOD2_ERR_HIP, "step counter could not be set");
       r->one_kernel = 1;
-    } catch (const sod2::Error& e) {
-      sod2::set_error(e.what());
-      return e.code;
-    } catch (const std::exception& e) {
-      sod2::set_error(e.what());
-      return SOD2_ERR_INVALID_ARG;
+      return SOD2_OK;
     }
-    return SOD2_OK;
+  } catch (const sod2::Error& e) {
+    sod2::set_error(e.what());
+    return e.code;
+  } catch (const std::exception& e) {
+    sod2::set_error(e.what());
+    return SOD2_ERR_INVALID_ARG;
   }
   if (launch_step_set(r->step, first_step, s) != hipSuccess) { sod2::set_error("step counter could not be set"); return SOD2_ERR_HIP; }
   for (int i = 0; i < n_steps; ++i)
@@ -2045,10 +2041,12 @@ static sod2_status run_impl(sod2_binding_t* h, void* arena, size_t arena_bytes, 
           if (h->launches[j].kernel == -2) h->launches[j] = first->make(p.groups.at(p.items[h->b.steps[j]].ref));
         h->launches_valid = true;
         Chain chain;
-        if (chain_build(h->launches, n_inputs, n_outputs, [&](const Ref& ref) { return P.at(ref); }, chain_workgroups(), 0, &chain)) {
+        if (chain_build(h->launches, n_inputs, n_outputs, [&](const Ref& ref) { return P.at(ref); }, chain_workgroups(s), 0, &chain)) {
           std::vector<void*> ext;
           for (int i = 0; i < n_inputs; ++i) ext.push_back((void*)inputs[i]);
           for (int i = 0; i < n_outputs; ++i) ext.push_back(outputs[i]);
+          chain.arrive_us = h->force_arrive_us;
+          chain.polls = h->force_polls;
           if (chain_fits(chain, ext.data())) {
             chain_launch(chain, ext.data(), chain.lk0, s);
             for (int at : h->b.steps) h->trace.push_back(sod2_trace_entry{1, p.items[at].ref, K_STEP, 0, 1, -1, 0});
