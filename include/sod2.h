@@ -301,7 +301,8 @@ sod2_status sod2_binding_set_constants(sod2_binding_t*, const void* constants_de
  * output that has no elements at the bound symbols may be NULL, any other NULL is SOD2_ERR_INVALID_ARG).
  * hip_stream: a hipStream_t (NULL = the null stream).  The first run of a graph with Switch, NonZero or NMS operators on
  * a host thread allocates one 64-byte slot of pinned, device-visible host memory (hipHostMalloc) for the read-backs;
- * it is kept until the process ends.  Nothing else is allocated by a run (launch records: events, created when
+ * it is kept until the process ends.  So does the first run of the process on a device that is one kernel (64 bytes and an
+ * event), also while another thread captures a stream.  Nothing else is allocated by a run (launch records: events, created when
  * profiling is switched on).  Enqueues and returns; the host waits for the
  * GPU only at a Switch, whose predicate it needs, and after a NonZero or NMS, whose count (8 bytes) sizes
  * what follows: a one-thread kernel behind the producing kernel publishes the value into pinned host

@@ -866,25 +866,33 @@ ChainDevice& chain_device() {
 void need(hipError_t e, const char* what) {
   if (e != hipSuccess) throw Error(SOD2_ERR_HIP, std::string(what) + ": " + hipGetErrorString(e));
 }
-void first_use(ChainDevice& d) {
-  if (d.known) return;
+// Addresses, a line of pinned memory and an event, once per device; false where they cannot be had (the groups run one by
+// one then).  Another thread may be capturing a stream meanwhile, which forbids every thread calls like these unless it
+// says that they are no part of the capture.
+bool first_use(ChainDevice& d) {
+  if (d.known) return true;
+  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+  const bool relaxed = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
   int dev = 0;
-  need(hipGetDevice(&dev), "current device");
-  need(hipDeviceGetAttribute(&d.n_cu, hipDeviceAttributeMultiprocessorCount, dev), "compute units");
-  void* p = nullptr;
-  need(hipGetSymbolAddress(&p, HIP_SYMBOL(chain_mail)), "address of the exchange buffer");
-  d.mail = (u64*)p;
-  need(hipGetSymbolAddress(&p, HIP_SYMBOL(chain_tables)), "address of the step tables");
-  d.tables = (ChainStep*)p;
-  need(hipGetSymbolAddress(&p, HIP_SYMBOL(chain_here)), "address of the counts of arrivals");
-  d.here = (unsigned*)p;
-  need(hipGetSymbolAddress(&p, HIP_SYMBOL(chain_rows)), "address of the lone workgroup's rows");
-  d.rows = (uint32_t*)p;
-  need(hipHostMalloc((void**)&d.err_host, 64, hipHostMallocCoherent | hipHostMallocMapped), "pinned host memory");
-  need(hipHostGetDevicePointer((void**)&d.err_dev, d.err_host, 0), "pinned host memory");
+  void *mail = nullptr, *tables = nullptr, *here = nullptr, *rows = nullptr;
+  bool ok = hipGetDevice(&dev) == hipSuccess && hipDeviceGetAttribute(&d.n_cu, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess &&
+            hipGetSymbolAddress(&mail, HIP_SYMBOL(chain_mail)) == hipSuccess && hipGetSymbolAddress(&tables, HIP_SYMBOL(chain_tables)) == hipSuccess &&
+            hipGetSymbolAddress(&here, HIP_SYMBOL(chain_here)) == hipSuccess && hipGetSymbolAddress(&rows, HIP_SYMBOL(chain_rows)) == hipSuccess;
+  if (ok && !d.err_host) ok = hipHostMalloc((void**)&d.err_host, 64, hipHostMallocCoherent | hipHostMallocMapped) == hipSuccess;
+  if (ok) ok = hipHostGetDevicePointer((void**)&d.err_dev, d.err_host, 0) == hipSuccess;
+  if (ok && !d.last) ok = hipEventCreateWithFlags(&d.last, hipEventDisableTiming) == hipSuccess;
+  if (relaxed) (void)hipThreadExchangeStreamCaptureMode(&mode);
+  if (!ok) {
+    (void)hipGetLastError();
+    return false;
+  }
+  d.mail = (u64*)mail;
+  d.tables = (ChainStep*)tables;
+  d.here = (unsigned*)here;
+  d.rows = (uint32_t*)rows;
   d.err_host[0] = d.err_host[1] = 0;
-  need(hipEventCreateWithFlags(&d.last, hipEventDisableTiming), "event");
   d.known = true;
+  return true;
 }
 }  // namespace
 
@@ -928,8 +936,7 @@ static bool masked(hipStream_t s, int n_cu) {
 int chain_workgroups(hipStream_t s) {
   ChainDevice& d = chain_device();
   std::lock_guard<std::mutex> lock(d.mu);
-  if (d.failed || !own_device(d)) return 0;
-  first_use(d);
+  if (d.failed || !own_device(d) || !first_use(d)) return 0;
   if (__atomic_load_n(&d.err_host[0], __ATOMIC_RELAXED)) {
     d.failed = true;
     throw Error(SOD2_ERR_HIP, "an earlier one-row step waited too long for another workgroup: its logits are NaN, and what was computed from them "
@@ -944,7 +951,7 @@ int chain_workgroups(hipStream_t s) {
 void chain_launch(const Chain& c, void* const* ext, int lk, hipStream_t s) {
   ChainDevice& d = chain_device();
   std::lock_guard<std::mutex> lock(d.mu);
-  first_use(d);
+  if (!d.known) throw Error(SOD2_ERR_HIP, "one-row step on a device that was not asked for one");
   // on the same stream too: a handle may by now be another stream's (destroyed and created again, or the per-thread one)
   if (d.any) need(hipStreamWaitEvent(s, d.last, 0), "ordering one-row steps of two streams");
   int slot = -1, oldest = 0;
