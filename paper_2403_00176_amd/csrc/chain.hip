@@ -932,8 +932,15 @@ static bool masked(hipStream_t s, int n_cu) {
 }
 
 // Workgroups a one-row step may have on stream s: one per CU, 0 where it is to be launched group by group.  Throws once
-// if an earlier step could not be brought to its end.
+// if an earlier step could not be brought to its end.  (A stream of another device than the calling thread's current one
+// launches kernels on its own device, where this device's exchange buffer and table have no business.)
 int chain_workgroups(hipStream_t s) {
+  hipDevice_t of_stream = -1;
+  int current = -2;
+  if (hipStreamGetDevice(s, &of_stream) != hipSuccess || hipGetDevice(&current) != hipSuccess || of_stream != current) {
+    (void)hipGetLastError();
+    return 0;
+  }
   ChainDevice& d = chain_device();
   std::lock_guard<std::mutex> lock(d.mu);
   if (d.failed || !own_device(d) || !first_use(d)) return 0;

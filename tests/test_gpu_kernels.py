@@ -184,6 +184,28 @@ def test_forced_and_profiled_decode_steps_run_group_by_group(S):
     torch.cuda.synchronize()
 
 
+# A session of a device that is not the calling thread's current one: its steps run group by group (the exchange buffer
+# and the step table are the current device's).
+def test_decode_step_of_another_device(S):
+    import torch
+    from paper_2403_00176_amd.session import DecoderSession
+    from workloads import configs
+    if torch.cuda.device_count() < 2:
+        pytest.skip("needs two GPUs")
+    w = configs.decoder(layers=2, hidden=256, heads=4, ffn=512, vocab=200, p_range=(1, 512), t_max=4, n_prompts=1)
+    logits = []
+    for device in ("cuda:0", "cuda:1"):
+        ses = DecoderSession(w.prefill, w.decode, w.t_max, device=device)
+        ses.upload_weights(w.make_weights_by_name())
+        ses.start(20, 200)
+        ses.prefill(torch.arange(20, device=ses.device))
+        assert torch.cuda.current_device() == 0
+        assert ran_as_one_kernel(S, ses.decode(0)) == (device == "cuda:0")
+        torch.cuda.synchronize(ses.device)
+        logits.append(ses.logits[1].float().cpu())
+    assert ((logits[0] - logits[1]).norm() / logits[0].norm()).item() <= 2 ** -8
+
+
 # Rows of nearly equal values whose squares overflow fp32 (1e19 and up) while the distances from their mean do not: the
 # LayerNorms of the one-kernel step take the variance from the distances, like those of the launches one by one.
 def test_decode_step_of_large_rows(S):
