@@ -10,7 +10,7 @@
 //  * gemm_simple: any dtype, any strides, plain FMA tiles (fp32 graphs, odd layouts).
 //  * conv_stem_kernel: convolutions with fewer than 8 input channels and 64 output channels.
 //  * gemm_f32_split: fp32 contractions on small grids, k split over the waves of a workgroup;
-//    gemv_f32_kernel: fp32 contractions of one row (the gate networks).
+//    gemv_f32_kernel: fp32 contractions of up to 4 rows (the gate networks).
 //  * row kernels: LayerNorm and softmax with one wavefront per row, 16-byte loads, wave shuffles.
 //  * reduce_mean (plain and wide), maxpool, elementwise chains (Fig. 4).
 //  * gather, cache append, arg-max; NonZero, ScatterRows, wide row gather (batch compaction);
@@ -1439,9 +1439,14 @@ hipError_t launch_conv_dl(const ConvArgs& c, const GemmArgs& g, int tile, hipStr
 hipError_t launch_gemv(const GemmArgs& g, hipStream_t s);
 hipError_t launch_gemm_ln(const GemmArgs& g, hipStream_t s);
 
-// fp32 contraction of a single row (the gate networks of the control-flow graphs): one wave per
-// output column, the lanes split k in 16-byte chunks of B[n, :], a shuffle tree finishes the sums
+// fp32 contraction of at most 4 rows (the gate networks of the control-flow graphs): one wave per output column, the
+// lanes split k in 16-byte chunks of B[n, :], a shuffle tree finishes the sums.  Bound by the latency of one column's
+// loads: U chunks of all operands are in flight at a time.  Two rows, K 4096: 64 columns 7.9 us with one chunk in flight,
+// 5.6 with four, 50000 columns 161 and 157; K 64 is one chunk, and the registers of four cost 12.8 us against 11.4
+// (one row, 50000 columns).
+template <int MR, int U>
 __global__ __launch_bounds__(256) void gemv_f32_kernel(GemmArgs g) {
+  typedef float f32x4_t __attribute__((ext_vector_type(4)));
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int n = blockIdx.x * 4 + wave;
   const int b0 = blockIdx.y / g.nb1, b1 = blockIdx.y % g.nb1;
@@ -1449,31 +1454,49 @@ __global__ __launch_bounds__(256) void gemv_f32_kernel(GemmArgs g) {
   const float* A = (const float*)g.A + b0 * g.a_sb0 + b1 * g.a_sb1;
   const float* B = (const float*)g.B + b0 * g.b_sb0 + b1 * g.b_sb1 + (long long)n * g.b_sn;
   const float bv = g.bias ? ((const float*)g.bias)[n] : 0.f;
-  float acc = 0.f;
-  const int nchunk = g.K >> 2;
-  const float4 z = make_float4(0.f, 0.f, 0.f, 0.f);
-  for (int c0 = lane; c0 < nchunk; c0 += 64 * 4) {       // 4 chunks of both operands in flight
-    float4 w[4], a[4];
+  float acc[MR];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
+  for (int m = 0; m < MR; ++m) acc[m] = 0.f;
+  const int nchunk = g.K >> 2;
+  const f32x4_t z = {0.f, 0.f, 0.f, 0.f};
+  for (int c0 = lane; c0 < nchunk; c0 += 64 * U) {
+    f32x4_t w[U], a[U][MR];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
       const int c = c0 + 64 * u;
-      w[u] = c < nchunk ? *(const float4*)(B + c * 4) : z;
-      a[u] = c < nchunk ? *(const float4*)(A + c * 4) : z;
+      w[u] = c < nchunk ? *(const f32x4_t*)(B + c * 4) : z;
+#pragma unroll
+      for (int m = 0; m < MR; ++m) a[u][m] = c < nchunk && m < g.M ? *(const f32x4_t*)(A + (long long)m * g.a_sm + c * 4) : z;
     }
 #pragma unroll
-    for (int u = 0; u < 4; ++u) acc = fmaf(a[u].x, w[u].x, fmaf(a[u].y, w[u].y, fmaf(a[u].z, w[u].z, fmaf(a[u].w, w[u].w, acc))));
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int m = 0; m < MR; ++m)
+        acc[m] = fmaf(a[u][m][0], w[u][0], fmaf(a[u][m][1], w[u][1], fmaf(a[u][m][2], w[u][2], fmaf(a[u][m][3], w[u][3], acc[m]))));
   }
-  acc = wave_sum(acc);
+#pragma unroll
+  for (int m = 0; m < MR; ++m) acc[m] = wave_sum(acc[m]);
   if (lane == 0) {
-    float v = apply_act(acc * g.scale + bv, g.act1);
-    if (g.res) v = apply_act(v + ((const float*)g.res + b0 * g.r_sb0 + b1 * g.r_sb1)[(long long)n * g.r_sn], g.act2);
-    ((float*)g.C + b0 * g.c_sb0 + b1 * g.c_sb1)[(long long)n * g.c_sn] = v;
+    const float* R = g.res ? (const float*)g.res + b0 * g.r_sb0 + b1 * g.r_sb1 : nullptr;
+    float* C = (float*)g.C + b0 * g.c_sb0 + b1 * g.c_sb1;
+#pragma unroll
+    for (int m = 0; m < MR; ++m) {
+      if (m < g.M) {
+        float v = apply_act(acc[m] * g.scale + bv, g.act1);
+        if (R) v = apply_act(v + R[(long long)m * g.r_sm + (long long)n * g.r_sn], g.act2);
+        C[(long long)m * g.c_sm + (long long)n * g.c_sn] = v;
+      }
+    }
   }
+}
+template <int MR, int U> static hipError_t launch_gemv_f32(const GemmArgs& g, hipStream_t s) {
+  hipLaunchKernelGGL((gemv_f32_kernel<MR, U>), dim3((g.N + 3) / 4, g.nb0 * g.nb1), dim3(256), 0, s, g);
+  return hipGetLastError();
 }
 
 static bool gemv_f32_ok(const Launch& L, const GemmArgs& g) {
   auto al = [](const void* p) { return ((uintptr_t)p & 15) == 0; };
-  return L.in_dtype != SOD2_BF16_TAG && L.out_dtype != SOD2_BF16_TAG && L.variant == V_GEMV && g.M <= 1 &&
+  return L.in_dtype != SOD2_BF16_TAG && L.out_dtype != SOD2_BF16_TAG && L.variant == V_GEMV && g.M <= 4 &&
          g.a_sk == 1 && g.b_sk == 1 && g.K % 4 == 0 && g.a_sm % 4 == 0 && g.b_sn % 4 == 0 && g.a_sb0 % 4 == 0 &&
          g.a_sb1 % 4 == 0 && g.b_sb0 % 4 == 0 && g.b_sb1 % 4 == 0 && al(g.A) && al(g.B);
 }
@@ -1487,32 +1510,49 @@ static hipError_t launch_f32_tile(const GemmArgs& g, bool av, bool bv, hipStream
   else hipLaunchKernelGGL((gemm_f32_split<T, T, false, false>), grid, block, 0, s, g);
   return hipGetLastError();
 }
-// fewer than 512 tiles of 64 x 64 (two per CU): the split-k kernel, with 16 x 16 tiles as long as those fit the chip
-// four workgroups to a CU, else 32 x 32 (half the operand traffic per result); from there on 64 x 64 FMA tiles fill
-// the chip and read each operand less often
-static hipError_t launch_gemm_f32_split(const GemmArgs& g, hipStream_t s) {
+// Which kernel an fp32 contraction takes.  t16, t32, t64: tiles of 16 x 16, 32 x 32 and 64 x 64 of all batches.
+//  * up to 16 rows: split-k kernel, 16 x 16 tiles (a taller tile multiplies rows that are not there).  8 rows, K 768: 16384
+//    columns 14.7 us (one wave per column 23.3), 50000 columns 39 us (67; 64 x 64 tiles 128).  Many short products (K <
+//    128, more than four workgroups to a CU: 16 rows, K 64, 50000 columns 16.9 us) leave its waves without work, 64 x 64
+//    tiles (16.5 us) do as well and are not slower on batches of smaller ones; with at most 8 rows of dense k it stays
+//    (6 rows 17.1 us; one wave per column 23.9).
+//  * up to 384 tiles of 16 x 16: those, the most workgroups (K 1024: 256 x 256 6.8 us, with 32 x 32 tiles 12.2); beyond
+//    them 32 x 32, half the operand traffic per result (512 x 512: 17.9 us with 16 x 16 tiles, 12.8 with 32 x 32; K 64:
+//    6.6 and 5.8).
+//  * 32 x 32 tiles against 64 x 64 on the vector units: a workgroup of eight waves that split k costs the same for any K up
+//    to 128, so more tiles than fit the chip at once (four to a CU) need a K to pay for them.  K 64: 700 x 700 (484 tiles)
+//    6.1 us against 10.2, 1400 x 1400 (1936) 18.0 against 12.6; 1400 x 1400: K 256 31.4 against 29.5, K 512 42.8 against
+//    51.6, K 4096 306 against 368; 1200 x 1200 (1444): K 128 20.0 against 17.6, K 256 24.1 against 28.8.  6 K >= t32 is on
+//    the better side of all of these.
+static hipError_t launch_gemm_f32(const GemmArgs& g, hipStream_t s) {
   auto al = [](const void* p) { return ((uintptr_t)p & 15) == 0; };
   const bool av = g.a_sk == 1 && g.K % 4 == 0 && g.a_sm % 4 == 0 && g.a_sb0 % 4 == 0 && g.a_sb1 % 4 == 0 && al(g.A);
   const bool bv = g.b_sk == 1 && g.K % 4 == 0 && g.b_sn % 4 == 0 && g.b_sb0 % 4 == 0 && g.b_sb1 % 4 == 0 && al(g.B);
-  const long long t16 = (long long)((g.M + 15) / 16) * ((g.N + 15) / 16) * g.nb0 * g.nb1;
-  return t16 <= 1024 ? launch_f32_tile<1>(g, av, bv, s) : launch_f32_tile<2>(g, av, bv, s);
+  auto tiles = [&](int t) { return (long long)((g.M + t - 1) / t) * ((g.N + t - 1) / t) * g.nb0 * g.nb1; };
+  const long long t16 = tiles(16), t32 = tiles(32), t64 = tiles(64);
+  if (g.M <= 16) {
+    if (t16 <= 1024 || g.K >= 128 || (g.M <= 8 && av && bv)) return launch_f32_tile<1>(g, av, bv, s);
+  } else {
+    if (t16 <= 384) return launch_f32_tile<1>(g, av, bv, s);
+    if (t32 <= 640 || (t64 < 512 && 6ll * g.K >= t32)) return launch_f32_tile<2>(g, av, bv, s);
+  }
+  hipLaunchKernelGGL(gemm_simple<float>, dim3(((g.M + 63) / 64) * ((g.N + 63) / 64), g.nb0 * g.nb1), dim3(256), 0, s, g);
+  return hipGetLastError();
 }
 
 hipError_t launch_gemm(const Launch& L, const GemmArgs& g, hipStream_t s) {
   if (g.ln_gamma) return L.in_dtype == SOD2_BF16_TAG ? launch_gemm_ln(g, s) : hipErrorInvalidValue;
   if (gemv_f32_ok(L, g)) {
-    hipLaunchKernelGGL(gemv_f32_kernel, dim3((g.N + 3) / 4, g.nb0 * g.nb1), dim3(256), 0, s, g);
-    return hipGetLastError();
+    if (g.K <= 256) return g.M <= 1 ? launch_gemv_f32<1, 1>(g, s) : launch_gemv_f32<4, 1>(g, s);      // one chunk per lane
+    return g.M <= 1 ? launch_gemv_f32<1, 4>(g, s) : (g.M <= 2 ? launch_gemv_f32<2, 4>(g, s) : launch_gemv_f32<4, 4>(g, s));
   }
   if (L.variant == V_GEMV && L.in_dtype == SOD2_BF16_TAG && g.a_vec && g.b_mode == 0 && g.M <= 8) return launch_gemv(g, s);
   if (L.variant >= V_DL0 && L.in_dtype == SOD2_BF16_TAG && g.a_vec && g.b_mode == 0 && dl_offsets_fit(g))
     return launch_gemm_dl(g, L.variant - V_DL0, s);
   if (g.fold) return hipErrorInvalidValue;                      // (no other kernel knows a folded LayerNorm)
-  if (L.variant == V_SIMPLE || L.in_dtype != SOD2_BF16_TAG) {
-    dim3 grid(((g.M + 63) / 64) * ((g.N + 63) / 64), g.nb0 * g.nb1);
-    if (L.in_dtype == SOD2_BF16_TAG) hipLaunchKernelGGL(gemm_simple<bf16_t>, grid, dim3(256), 0, s, g);
-    else if (grid.x * grid.y < 512) return launch_gemm_f32_split(g, s);
-    else hipLaunchKernelGGL(gemm_simple<float>, grid, dim3(256), 0, s, g);
+  if (L.in_dtype != SOD2_BF16_TAG) return launch_gemm_f32(g, s);
+  if (L.variant == V_SIMPLE) {
+    hipLaunchKernelGGL(gemm_simple<bf16_t>, dim3(((g.M + 63) / 64) * ((g.N + 63) / 64), g.nb0 * g.nb1), dim3(256), 0, s, g);
     return hipGetLastError();
   }
   MatA al{(const bf16_t*)g.A, g.a_sm, g.a_sk, g.M, g.K, g.a_vec};

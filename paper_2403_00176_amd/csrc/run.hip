@@ -316,7 +316,7 @@ struct Builder {
   // and two workgroups per CU otherwise); below that the 64 x 64 x 64 tile with a four-stage ring
   // puts more workgroups (more loads in flight) on the chip.
   int pick_variant(int dtype, int64_t M, int64_t N, int64_t K, int64_t batch) const {
-    if (dtype != SOD2_BF16) return (M <= 8 && force_variant != V_SIMPLE && p.opts.mvc) ? V_GEMV : V_SIMPLE;   // fp32: plain FMA kernels
+    if (dtype != SOD2_BF16) return (M <= 8 && force_variant != V_SIMPLE && p.opts.mvc) ? V_GEMV : V_SIMPLE;   // fp32: launch_gemm picks the kernel
     if (force_variant >= 0) return force_variant;
     // multi-version kernels off (the breakdown study of Section 5.3): one version of the same kernel for every
     // shape -- the 128 x 128 x 64 tile, no skinny version, no k groups, no split-K

@@ -27,11 +27,15 @@ def run_graph(graph, sym, weights, inputs, sessions=None):
     return [to_host(o) for o in outs]
 
 
-# fp32 contractions: 16 x 16 tiles with k split over 8 waves (rows and columns of one tile and one more, k shorter than
-# one chunk per wave, k not a multiple of 4, k longer than one round of loads), 32 x 32 tiles, 64 x 64 FMA tiles
+# fp32 contractions: a wave per column for 1, 2 and up to 4 rows (k of one chunk per lane and of more, columns that are no
+# multiple of 4), 16 x 16 tiles with k split over 8 waves (rows and columns of one tile and one more, k shorter than one
+# chunk per wave, k not a multiple of 4, k longer than one round of loads; few rows of many columns), 32 x 32 tiles, 64 x
+# 64 FMA tiles (also where the k of a full chip is short)
 @pytest.mark.parametrize("M,N,K,trans_b,batch", [
     (2, 64, 768, 1, 1), (8, 1, 64, 1, 1), (16, 16, 16, 1, 1), (17, 15, 77, 0, 3), (77, 77, 64, 1, 4), (77, 64, 77, 0, 4),
-    (33, 47, 1030, 1, 1), (128, 1024, 256, 1, 1), (513, 545, 260, 1, 1), (300, 300, 131, 0, 4), (1473, 1409, 40, 1, 1)])
+    (33, 47, 1030, 1, 1), (128, 1024, 256, 1, 1), (513, 545, 260, 1, 1), (300, 300, 131, 0, 4), (1473, 1409, 40, 1, 1),
+    (1, 101, 256, 1, 1), (1, 99, 1300, 1, 1), (2, 33, 260, 1, 1), (3, 50, 256, 1, 1), (3, 50, 1028, 1, 1), (4, 7, 64, 1, 1),
+    (6, 17000, 64, 1, 1), (16, 17000, 24, 1, 1), (16, 17000, 128, 1, 1), (385, 383, 68, 1, 1), (690, 1200, 140, 1, 1), (1000, 1100, 64, 1, 1)])
 def test_fp32_contraction(S, M, N, K, trans_b, batch):
     from workloads import GraphBuilder
     print(f"case M {M} N {N} K {K} transB {trans_b} batch {batch}", flush=True)
