@@ -106,6 +106,13 @@ def test_contraction_of_a_broadcast_row(S, M, K, folded):
 STEP = 23                                          # kernel of a trace entry: a phase of a step that ran as one kernel
 
 
+def cache_offsets(S, desc, binding):
+    """Where the cached keys and values of every layer lie: the session slots of the CacheAppend results."""
+    at = [S.sod2_binding_query_tensor(binding, op.outputs[0]) for op in desc.ops if op.kind == "CacheAppend"]
+    assert all(i["where"] == "session" for i in at) and len({i["offset"] for i in at}) == len(at) == len(desc.session_inputs())
+    return [i["offset"] for i in at]
+
+
 def ran_as_one_kernel(S, binding):
     kernels = {e["kernel"] for e in S.sod2_run_trace(binding)}
     assert kernels == {STEP} or STEP not in kernels
@@ -144,7 +151,7 @@ def test_decode_step_as_one_kernel(S, hidden, heads, ffn, vocab, P):
         torch.cuda.synchronize()
         d = w.decode
         caches = [ses.arena[at:at + (P + steps) * hidden * 2].view(torch.bfloat16).float().clone()
-                  for at in (S.sod2_binding_query_tensor(b, t)["offset"] for t in d.session_inputs())]
+                  for at in cache_offsets(S, d, b)]
         return ses.logits[1:steps + 1].float().clone(), ses.tokens[P + 1:P + steps + 1].clone(), caches
 
     ref, one = run(True), run(False)

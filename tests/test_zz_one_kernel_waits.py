@@ -53,7 +53,9 @@ class Sequence:
         torch.cuda.synchronize()
         n = self.P + self.steps
         cache = [self.ses.arena[at:at + n * self.hidden * 2].view(torch.bfloat16).double().clone()
-                 for at in (self.S.sod2_binding_query_tensor(self.last, t)["offset"] for t in self.w.decode.session_inputs())]
+                 for at in (self.S.sod2_binding_query_tensor(self.last, op.outputs[0])["offset"]       # (the session slots)
+                            for op in self.w.decode.ops if op.kind == "CacheAppend")]
+        assert len(cache) == 4
         return self.ses.logits[1:self.steps + 1].double().clone(), cache
 
 
