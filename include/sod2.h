@@ -313,7 +313,7 @@ sod2_status sod2_binding_set_constants(sod2_binding_t*, const void* constants_de
  * kernels do not support, an arena too small for the path taken) the groups before the failing one
  * may have run and the contents of the outputs and of the arena are unspecified.
  * A graph whose executed groups form a chain of one-row work (a decode step) runs as one kernel, with sums in another
- * order than the groups launched one by one; it takes the groups under capture, with a version or a number of k ranges
+ * order than the groups launched one by one, and its intermediate results do not reach the arena; it takes the groups under capture, with a version or a number of k ranges
  * forced, while profiled, on a stream with a CU mask, where a second process runs such graphs on the device, and for some
  * seconds after its workgroups could not start together (see sod2_binding_force_waits). */
 sod2_status sod2_run(sod2_binding_t*, void* arena_dev, size_t arena_bytes,

@@ -931,6 +931,16 @@ static bool masked(hipStream_t s, int n_cu) {
   return bits > 0 && bits < n_cu;
 }
 
+// CUs of the current device: what a replay's table is dealt out to, whether the kernel can be had just now or not
+int chain_cus() {
+  int dev = 0, n = 0;
+  if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) {
+    (void)hipGetLastError();
+    return 0;
+  }
+  return n;
+}
+
 // Workgroups a one-row step may have on stream s: one per CU, 0 where it is to be launched group by group.  Throws once
 // if an earlier step could not be brought to its end.  (A stream of another device than the calling thread's current one
 // launches kernels on its own device, where this device's exchange buffer and table have no business.)

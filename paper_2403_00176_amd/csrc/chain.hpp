@@ -35,6 +35,7 @@ struct Chain {
   int arrive_us = -1, polls = -1;      // limits of the waits between its workgroups, -1: the kernel's own
 };
 
+int chain_cus();
 int chain_workgroups(hipStream_t s);
 bool chain_build(const std::vector<Launch>& launches, int n_in, int n_out, const std::function<void*(const Ref&)>& at, int n_cu, int lk_grows,
                  Chain* out);

@@ -1831,7 +1831,7 @@ extern "C" sod2_status sod2_replay_create(const sod2_plan_t* ph, const int64_t* 
         if (r->d_lk == 0) r->d_lk = L.d_lk;
         same_growth = same_growth && L.d_lk == r->d_lk;
       }
-    if (same_growth && chain_build(L0, n_inputs, n_outputs, [&](const Ref& ref) { return P.at(ref); }, chain_workgroups(s),
+    if (same_growth && chain_build(L0, n_inputs, n_outputs, [&](const Ref& ref) { return P.at(ref); }, chain_cus(),
                                    r->d_lk * (max_steps - 1), &r->chain)) {
       for (int i = 0; i < n_inputs; ++i) { r->ext.push_back((char*)inputs[i]); r->ext_step.push_back(P.in_step[i]); }
       for (int i = 0; i < n_outputs; ++i) { r->ext.push_back((char*)outputs[i]); r->ext_step.push_back(P.out_step[i]); }
