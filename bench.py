@@ -68,8 +68,8 @@ def bench_ablation(args, S, dev):
 
 def bench_decoder(args, S, dev):
     """Config 5 (not the headline workload): per sequence one prompt pass and `t_max` greedy decode steps, the
-    next token read on the device; reports ms per generated token (steps replayed from one captured HIP
-    graph, and bound and launched one by one) and the prompt-pass latency."""
+    next token read on the device; reports ms per generated token (steps replayed without planning on the
+    host, and bound and launched one by one) and the prompt-pass latency."""
     import numpy as np
     import torch
     from paper_2403_00176_amd.session import DecoderSession

@@ -391,7 +391,7 @@ sod2_status sod2_binding_launch_records(const sod2_binding_t*, sod2_launch_recor
  * length of its KV cache) and whose launch sequence depends on that symbol only through the row a
  * CacheAppend writes and the number of keys a few-query attention reads: the launches of one step are
  * captured once in a HIP graph; the kernels read the step from a counter in device memory, so each
- * further step costs one graph launch and no host planning.  symbols_host are the values of step 0;
+ * further step costs one graph launch, or one kernel (see sod2_run), and no host planning.  symbols_host are the values of step 0;
  * inputs / outputs are the device pointers of step 0 and *_step_bytes (host, one per pointer, may be
  * NULL) the bytes each advances per step; step_counter_dev is one int32 of device memory the caller
  * keeps alive.  The arena must hold the plan of the last step.  hip_stream must not be the null stream.

@@ -830,7 +830,7 @@ __global__ __launch_bounds__(256) void chain_clear_kernel(u64* mail, long long n
   for (long long i = (long long)blockIdx.x * 256 + threadIdx.x; i < n; i += 256ll * gridDim.x) mail[i] = 0;
 }
 
-constexpr int CH_TABLES = 8;
+constexpr int CH_TABLES = 8;       // sequences whose tables stay on the device; one more is uploaded again, 5 small launches a step (24 layers)
 static __device__ __align__(256) u64 chain_mail[CH_RING * CH_REGION];
 static __device__ __align__(256) ChainStep chain_tables[CH_TABLES][CHAIN_MAX_STEPS];
 static __device__ __align__(256) unsigned chain_here[2][64];               // arrivals of this launch and the next

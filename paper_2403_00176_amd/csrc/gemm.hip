@@ -230,8 +230,6 @@ __global__ __launch_bounds__(LW * KG * 64, OCC * LW * KG / 4) void gemm_dl(AL al
                     (BM + BN) * KV % NT == 0 && BM % (64 / KV) == 0 && (KG == 1 || LW == NCW),
                 "4 or 8 compute waves per group, at most 16 waves");
   static_assert((ST - 2) * LT <= 63, "vmcnt is a 6-bit counter");
-  // behind the ring: FOLD 1 the tile's BN values of gamma; FOLD 2 per tile row (scale * rstd, -scale * rstd * mean),
-  // then the tile's BN values of fold_s and of fold_c (staged here so that no register holds them through the k loop)
   // behind the ring: FOLD 1 the tile's BN values of gamma; FOLD 2 the tile's BN values of fold_s and of fold_c, then per
   // tile row (scale * rstd, -scale * rstd * mean).  (In LDS, so that no register holds them through the k loop.)
   constexpr int AUX = FOLD == 2 ? 1024 * ((BN + 127) / 128) : (FOLD == 1 ? 1024 : 0);     // bytes: whole 1 KB loads

@@ -128,7 +128,7 @@ class DecoderSession:
         self.dec = Session(decode_desc, device, **plan_opts)
         self.t_max = int(t_max)
         self.device = self.pre.device
-        # a stream of its own (default priority): the decode steps can be captured in a HIP graph, which the
+        # a stream of its own (default priority): the decode steps are captured in a HIP graph, which the
         # null stream does not allow.  Callers do their own torch work inside `with torch.cuda.stream(ses.stream)`.
         self.stream = torch.cuda.Stream(self.device)
         self.pre.stream = self.dec.stream = self.stream
@@ -188,8 +188,8 @@ class DecoderSession:
         return b
 
     def decode_replay(self, first_step: int, n_steps: int):
-        """Steps first_step .. first_step + n_steps - 1 as replays of one captured HIP graph: the kernels
-        read the step from a counter on the device, the host plans nothing per step."""
+        """Steps first_step .. first_step + n_steps - 1 without planning on the host: each as one kernel, or as a replay of
+        one captured HIP graph whose kernels read the step from a counter on the device (sod2_replay_one_kernel)."""
         P, d = self.P, self.dec.desc
         if self.replay is None:
             row = self.logits.stride(0) * self.logits.element_size()
