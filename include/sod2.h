@@ -314,8 +314,11 @@ sod2_status sod2_binding_set_constants(sod2_binding_t*, const void* constants_de
  * may have run and the contents of the outputs and of the arena are unspecified.
  * A graph whose executed groups form a chain of one-row work (a decode step) runs as one kernel, with sums in another
  * order than the groups launched one by one, and its intermediate results do not reach the arena; it takes the groups under capture, with a version or a number of k ranges
- * forced, while profiled, on a stream with a CU mask, where a second process runs such graphs on the device, and for some
- * seconds after its workgroups could not start together (see sod2_binding_force_waits). */
+ * forced, while profiled, on a stream with a CU mask or a special handle other than NULL, where a second process runs such graphs on the device, and for some
+ * seconds after its workgroups could not start together (see sod2_binding_force_waits).  One such kernel fills the
+ * device, so those of different streams of a process run in the order of their calls: each waits for the one before it.
+ * A program that holds a stream back until another stream's later run of this kind is done has to force a version on one
+ * of the two. */
 sod2_status sod2_run(sod2_binding_t*, void* arena_dev, size_t arena_bytes,
                      const void* const* weights_dev, int32_t n_weights,
                      const void* const* inputs_dev, int32_t n_inputs,

@@ -945,11 +945,14 @@ int chain_cus() {
 // if an earlier step could not be brought to its end.  (A stream of another device than the calling thread's current one
 // launches kernels on its own device, where this device's exchange buffer and table have no business.)
 int chain_workgroups(hipStream_t s) {
-  hipDevice_t of_stream = -1;
-  int current = -2;
-  if (hipStreamGetDevice(s, &of_stream) != hipSuccess || hipGetDevice(&current) != hipSuccess || of_stream != current) {
-    (void)hipGetLastError();
-    return 0;
+  if (!chain_takes(s)) return 0;
+  if (s) {                                  // (the null stream is the current device's, with all its CUs)
+    hipDevice_t of_stream = -1;
+    int current = -2;
+    if (hipStreamGetDevice(s, &of_stream) != hipSuccess || hipGetDevice(&current) != hipSuccess || of_stream != current) {
+      (void)hipGetLastError();
+      return 0;
+    }
   }
   ChainDevice& d = chain_device();
   std::lock_guard<std::mutex> lock(d.mu);
@@ -961,7 +964,7 @@ int chain_workgroups(hipStream_t s) {
   }
   const auto now = std::chrono::steady_clock::now();
   if (__atomic_exchange_n(&d.err_host[1], 0u, __ATOMIC_RELAXED)) d.again = now + std::chrono::seconds(CH_REST);
-  return now < d.again || masked(s, d.n_cu) ? 0 : d.n_cu;
+  return now < d.again || (s && masked(s, d.n_cu)) ? 0 : d.n_cu;
 }
 
 // One step on stream s.  ext: the caller's input and output pointers; lk: keys of the attention phases with lk_rel 0.

@@ -35,6 +35,9 @@ struct Chain {
   int arrive_us = -1, polls = -1;      // limits of the waits between its workgroups, -1: the kernel's own
 };
 
+// The special stream handles besides NULL stay with the launches group by group, which ask the runtime nothing about a
+// stream: not every runtime answers for them.
+inline bool chain_takes(hipStream_t s) { return s != hipStreamLegacy && s != hipStreamPerThread; }
 int chain_cus();
 int chain_workgroups(hipStream_t s);
 bool chain_build(const std::vector<Launch>& launches, int n_in, int n_out, const std::function<void*(const Ref&)>& at, int n_cu, int lk_grows,

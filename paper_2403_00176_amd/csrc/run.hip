@@ -1870,8 +1870,9 @@ extern "C" sod2_status sod2_replay_launch(sod2_replay_t* r, int32_t first_step, 
   // one kernel per step, but not under capture: a captured launch run again would carry the tags of its first run
   try {
     hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-    if (r->chained && hipStreamIsCapturing(s, &capture) != hipSuccess) { (void)hipGetLastError(); capture = hipStreamCaptureStatusActive; }
-    if (r->chained && capture == hipStreamCaptureStatusNone && chain_workgroups(s) >= r->chain.workgroups) {
+    const bool chained = r->chained && chain_takes(s);
+    if (chained && hipStreamIsCapturing(s, &capture) != hipSuccess) { (void)hipGetLastError(); capture = hipStreamCaptureStatusActive; }
+    if (chained && capture == hipStreamCaptureStatusNone && chain_workgroups(s) >= r->chain.workgroups) {
       std::vector<void*> ext(r->ext.size());
       for (int i = first_step; i < first_step + n_steps; ++i) {
         for (size_t k = 0; k < ext.size(); ++k) ext[k] = r->ext[k] + r->ext_step[k] * i;
@@ -2033,7 +2034,7 @@ static sod2_status run_impl(sod2_binding_t* h, void* arena, size_t arena_bytes, 
 
     // One-row work from end to end (a decode step) runs as one kernel.  Not under capture: a replayed launch would carry
     // the tags of the captured one.
-    if (!static_ws && !ev && h->force_variant < 0 && h->force_splits == 0 && p.opts.mvc && may_chain(p, h->b)) {
+    if (!static_ws && !ev && h->force_variant < 0 && h->force_splits == 0 && p.opts.mvc && chain_takes(s) && may_chain(p, h->b)) {
       hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
       if (hipStreamIsCapturing(s, &capture) != hipSuccess) { (void)hipGetLastError(); capture = hipStreamCaptureStatusActive; }
       if (capture == hipStreamCaptureStatusNone) {

@@ -195,6 +195,27 @@ def test_forced_and_profiled_decode_steps_run_group_by_group(S):
     torch.cuda.synchronize()
 
 
+# The null stream takes the one-kernel step like any other stream of the device.
+def test_decode_step_on_the_null_stream(S):
+    import torch
+    from paper_2403_00176_amd.session import DecoderSession
+    from workloads import configs
+    w = configs.decoder(layers=2, hidden=256, heads=4, ffn=512, vocab=200, p_range=(1, 512), t_max=4, n_prompts=1)
+    ses = DecoderSession(w.prefill, w.decode, w.t_max)
+    ses.upload_weights(w.make_weights_by_name())
+    ses.start(20, 200)
+    ses.prefill(torch.arange(20, device=ses.device))
+    ses.decode(0)
+    torch.cuda.synchronize()
+    row = ses.logits[1].clone()
+    ses.logits[1].zero_()
+    ses.stream = ses.dec.stream = torch.cuda.default_stream()
+    assert ses.stream.cuda_stream == 0
+    assert ran_as_one_kernel(S, ses.decode(0))
+    torch.cuda.synchronize()
+    assert torch.equal(row, ses.logits[1])
+
+
 # A session of a device that is not the calling thread's current one: its steps run group by group (the exchange buffer
 # and the step table are the current device's).
 def test_decode_step_of_another_device(S):

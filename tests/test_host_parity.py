@@ -151,6 +151,12 @@ def test_forced_versions_are_the_built_ones():
         with pytest.raises(S.Sod2Error) as e:
             S.sod2_binding_force_variant(b, v)
         assert e.value.code == -1
+    S.sod2_binding_force_waits(b, arrive_us=0, polls=1)
+    S.sod2_binding_force_waits(b)
+    for bad in [dict(arrive_us=-2), dict(arrive_us=40000001), dict(polls=-2)]:
+        with pytest.raises(S.Sod2Error) as e:
+            S.sod2_binding_force_waits(b, **bad)
+        assert e.value.code == -1
 
 
 def test_tiny_fixture_graphs_match_oracle():
