@@ -1530,9 +1530,9 @@ static hipError_t launch_gemm_f32(const GemmArgs& g, hipStream_t s) {
   const bool bv = g.b_sk == 1 && g.K % 4 == 0 && g.b_sn % 4 == 0 && g.b_sb0 % 4 == 0 && g.b_sb1 % 4 == 0 && al(g.B);
   auto tiles = [&](int t) { return (long long)((g.M + t - 1) / t) * ((g.N + t - 1) / t) * g.nb0 * g.nb1; };
   const long long t16 = tiles(16), t32 = tiles(32), t64 = tiles(64);
-  if (g.M <= 16) {
+  if (!g.fma_tiles && g.M <= 16) {
     if (t16 <= 1024 || g.K >= 128 || (g.M <= 8 && av && bv)) return launch_f32_tile<1>(g, av, bv, s);
-  } else {
+  } else if (!g.fma_tiles) {
     if (t16 <= 384) return launch_f32_tile<1>(g, av, bv, s);
     if (t32 <= 640 || (t64 < 512 && 6ll * g.K >= t32)) return launch_f32_tile<2>(g, av, bv, s);
   }

@@ -39,6 +39,7 @@ struct GemmArgs {
   int act1, act2;
   int a_vec, b_mode;       // a_vec: 16-byte loads along k allowed; b_mode 0 k-contiguous vec, 1 n-contiguous vec, 2 scalar
   int c_vec;               // c_sn == 1 and rows 4-byte aligned
+  int fma_tiles;           // fp32: the plain FMA kernel whatever the shape (that version forced, or multi-version kernels off)
   int splits;              // > 1: split-K, fp32 partials in ws, summed in z order by a second kernel
   int group_m;             // tile rows per panel of the tile walk (L2 locality)
   QuickDiv d_panel, d_group, d_last;   // tiles of a panel; rows of a panel, of the last panel

@@ -448,6 +448,7 @@ struct Builder {
     if (e.res >= 0) L.r[4] = ref_of(view_of(e.res), dt);
     int64_t batch = (int64_t)g.nb0 * g.nb1;
     L.variant = pick_variant(dt, g.M, g.N, g.K, batch);
+    g.fma_tiles = dt != SOD2_BF16 && (force_variant == V_SIMPLE || !p.opts.mvc);
     // the one tile of the shape rule that cannot write or read a folded LayerNorm gives way to its neighbour
     if (folding && force_variant < 0 && L.variant == V_DL0 + DL_128x128x64_S2_W8G2 &&
         ((!gr.also.empty() && p.fold_y[gr.also[0]] >= 0) || gr.lnfold >= 0))

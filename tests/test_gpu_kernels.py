@@ -57,6 +57,30 @@ def test_fp32_contraction(S, M, N, K, trans_b, batch):
     assert got.shape == ref.shape and (np.abs(got - ref) <= bound).all(), np.max(np.abs(got - ref) / bound)
 
 
+# The plain FMA kernel is one version for every shape: the forced version 3 and a plan without multi-version kernels give
+# the same bits, where the automatic choice splits k and so sums in another order.
+@pytest.mark.parametrize("M,K", [(2, 768), (77, 1024)])
+def test_fp32_plain_version(S, M, K):
+    import torch
+    from paper_2403_00176_amd.session import Session
+    from workloads import GraphBuilder
+    rs = np.random.RandomState(M)
+    X, W, got = rs.randn(M, K), rs.randn(256, K), {}
+    for how in ("automatic", "forced", "one version"):
+        gb = GraphBuilder([("M", 1, 2048)])
+        x, w = gb.input("x", "f32", ["M", K]), gb.weight("w", "f32", [256, K])
+        gb.mark_output(gb.op("MatMul", [x, w], transB=1), "y")
+        ses = Session(gb.build(), mvc=0 if how == "one version" else 1)
+        ses.upload_weights({w: W})
+        b = ses.bind({"M": M})
+        S.sod2_binding_force_variant(b, 3 if how == "forced" else -1)
+        outs = ses.alloc_outputs(ses.output_shapes(b))
+        ses.run(b, ses.upload_inputs({x: X}), outs)
+        torch.cuda.synchronize()
+        got[how] = outs[0]
+    assert torch.equal(got["forced"], got["one version"]) and not torch.equal(got["forced"], got["automatic"])
+
+
 # A contraction whose first operand repeats one row (an Expand: row stride 0), plain (with k split over workgroups) and
 # with the LayerNorm behind it folded into it and into the contraction that reads it.
 @pytest.mark.parametrize("M,K,folded", [(512, 256, True), (333, 768, True), (64, 4096, False)])
