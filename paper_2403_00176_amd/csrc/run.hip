@@ -1826,7 +1826,7 @@ extern "C" sod2_status sod2_replay_create(const sod2_plan_t* ph, const int64_t* 
     r->step = step_counter;
     r->max_steps = max_steps;
     hipStream_t s = (hipStream_t)stream;
-    bool same_growth = may_chain(p, b0);
+    bool same_growth = p.opts.mvc && may_chain(p, b0);       // (as in sod2_run)
     for (const Launch& L : L0)
       if (L.kernel == K_ATTENTION) {
         if (r->d_lk == 0) r->d_lk = L.d_lk;

@@ -16,7 +16,7 @@ def test_first_step_while_another_thread_captures(S_lib):
     ses = DecoderSession(w.prefill, w.decode, w.t_max)
     ses.upload_weights(w.make_weights_by_name())
     ses.start(20, 200)
-    ses.prefill(torch.arange(20, device=ses.device))
+    ses.prefill(torch.arange(20).to(ses.device))
     x = torch.zeros(1000, device=ses.device)
     torch.cuda.synchronize()
     result = []

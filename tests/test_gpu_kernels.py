@@ -209,7 +209,7 @@ def test_forced_and_profiled_decode_steps_run_group_by_group(S):
     ses = DecoderSession(w.prefill, w.decode, w.t_max)
     ses.upload_weights(w.make_weights_by_name())
     ses.start(20, 200)
-    ses.prefill(torch.arange(20, device=ses.device))
+    ses.prefill(torch.arange(20).to(ses.device))
     for force, one in [(lambda b: None, True), (lambda b: S.sod2_binding_force_variant(b, 6), False),
                        (lambda b: S.sod2_binding_force_splits(b, 2), False), (lambda b: S.sod2_binding_set_profiling(b, True), False)]:
         b = ses.dec.bind({"P": 20, "t": 0})
@@ -217,6 +217,35 @@ def test_forced_and_profiled_decode_steps_run_group_by_group(S):
         ses.decode(0, b)
         assert ran_as_one_kernel(S, b) == one
     torch.cuda.synchronize()
+
+
+# A plan without multi-version kernels has one version of every contraction: neither its runs nor its replays are one kernel.
+def test_decode_step_of_a_plan_of_one_version(S):
+    import torch
+    from paper_2403_00176_amd.session import DecoderSession
+    from workloads import configs
+    w = configs.decoder(layers=2, hidden=256, heads=4, ffn=512, vocab=200, p_range=(1, 512), t_max=4, n_prompts=1)
+    ses = DecoderSession(w.prefill, w.decode, w.t_max, mvc=0)
+    ses.upload_weights(w.make_weights_by_name())
+    ses.start(20, 200)
+    ses.prefill(torch.arange(20).to(ses.device))
+    assert not ran_as_one_kernel(S, ses.decode(0))
+    d = w.decode
+    fixed = [0] * len(d.inputs()), [0] * len(d.outputs())      # (nothing that moves: only skinny contractions follow a moving result)
+    ins = {"ids": ses.tokens[20:], "pos": ses.positions[20:]}
+    outs = {"logits": ses.logits[1], "next": ses.tokens[21:]}
+    replay = S.sod2_replay_create(ses.dec.plan, {"P": 20, "t": 0}, "t", 4, ses.arena.data_ptr(), ses.arena.numel(),
+                                  [x.data_ptr() for x in ses.dec.weights], [ins[d.tensors[t].name].data_ptr() for t in d.inputs()], fixed[0],
+                                  [outs[d.tensors[t].name].data_ptr() for t in d.outputs()], fixed[1], ses.step_counter.data_ptr(),
+                                  ses.stream.cuda_stream)
+    torch.cuda.synchronize()
+    row = ses.logits[1].clone()
+    ses.logits[1].zero_()
+    torch.cuda.synchronize()
+    S.sod2_replay_launch(replay, 0, 1, ses.stream.cuda_stream)
+    assert not S.sod2_replay_one_kernel(replay)
+    torch.cuda.synchronize()
+    assert torch.equal(row, ses.logits[1])
 
 
 # The null stream takes the one-kernel step like any other stream of the device.
@@ -228,11 +257,12 @@ def test_decode_step_on_the_null_stream(S):
     ses = DecoderSession(w.prefill, w.decode, w.t_max)
     ses.upload_weights(w.make_weights_by_name())
     ses.start(20, 200)
-    ses.prefill(torch.arange(20, device=ses.device))
+    ses.prefill(torch.arange(20).to(ses.device))
     ses.decode(0)
     torch.cuda.synchronize()
     row = ses.logits[1].clone()
     ses.logits[1].zero_()
+    torch.cuda.synchronize()
     ses.stream = ses.dec.stream = torch.cuda.default_stream()
     assert ses.stream.cuda_stream == 0
     assert ran_as_one_kernel(S, ses.decode(0))
@@ -254,7 +284,7 @@ def test_decode_step_of_another_device(S):
         ses = DecoderSession(w.prefill, w.decode, w.t_max, device=device)
         ses.upload_weights(w.make_weights_by_name())
         ses.start(20, 200)
-        ses.prefill(torch.arange(20, device=ses.device))
+        ses.prefill(torch.arange(20).to(ses.device))
         assert torch.cuda.current_device() == 0
         assert ran_as_one_kernel(S, ses.decode(0)) == (device == "cuda:0")
         torch.cuda.synchronize(ses.device)

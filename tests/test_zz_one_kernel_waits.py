@@ -87,6 +87,7 @@ def test_step_done_by_one_workgroup(S, hidden, heads, ffn, vocab, P):
         assert not seq.step(t, variant=6)
     ref = seq.state()
     seq.ses.logits.zero_()
+    torch.cuda.synchronize()
     assert seq.step(0, arrive_us=0)
     torch.cuda.synchronize()
     first = seq.ses.logits[1].float()
@@ -163,6 +164,7 @@ def test_wait_past_its_limit_is_reported(S):
         seq.step(t, variant=6)
     ref = seq.state()
     seq.ses.logits.zero_()
+    torch.cuda.synchronize()
     assert seq.step(0, polls=1)
     torch.cuda.synchronize()
     assert torch.isnan(seq.ses.logits[1]).all()
